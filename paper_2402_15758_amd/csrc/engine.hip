@@ -119,6 +119,8 @@ struct chimera_model {
 // Encoder memory per sequence and stream: positions 0 .. max_len + 63, then
 // (stream 1) one slot per draft-tree node for the speculative trigram entries.
 constexpr int ENC_TREE_SLOTS = 64;
+// Largest prefill chunk, in rows.
+constexpr int PREFILL_ROWS = 2048;
 
 struct chimera_kv {
   chimera_model* m = nullptr;
@@ -150,7 +152,7 @@ struct Event2 {
 struct chimera_ctx {
   chimera_model* m = nullptr;
   chimera_kv* kv = nullptr;
-  int B = 0, N = 0, K = 0, D = 0, Mv = 0, Md = 0, Mq = 0, G = 0, nblk_enc = 0, tok_stride = 0;
+  int B = 0, N = 0, K = 0, D = 0, Mv = 0, Md = 0, Mq = 0, Mp = 0, G = 0, nblk_enc = 0, tok_stride = 0;
   std::vector<int> parent, rank, depth, s_k;
   std::vector<unsigned long long> anc;
   TreeMeta tree, chain;
@@ -174,8 +176,8 @@ struct chimera_ctx {
   int* pro_base = nullptr;
   int* pro_count = nullptr;
   void* pro_h = nullptr;
-  int* pf_n = nullptr;
   int* pf_tokens = nullptr;
+  PrefillBlock* pf_blk = nullptr;
   // verify workspaces
   float* x = nullptr;
   void* xn = nullptr;
@@ -342,7 +344,6 @@ struct Gemm {
     else
       launch_gemm(c->m->dt, s, e, st);
   }
-  int splits(int N, int K) const { return gemm_pick_splits(N, K, c->m->dt); }
 };
 
 struct VerifyRows {
@@ -353,6 +354,8 @@ struct VerifyRows {
   const int* depth;
   const uint8_t* path;
   int N, D, B;
+  int mtiles;                // 16-row tiles of the activation buffers
+  const PrefillBlock* blk;   // prefill: B query blocks; nullptr: B trees of N nodes
 };
 
 // Target layer stack over M rows; leaves the post-final-norm states in c->hl.
@@ -364,11 +367,11 @@ void verify_layers(chimera_ctx* c, const VerifyRows& r, hipStream_t st, bool tim
   const int hdim = H * hd;
   const Gemm g{c, st, timed};
   launch_embed(dt, r.tokens, m->embed, c->x, r.M, d, cf.vocab, st);
-  launch_attn_rows(r.n_b, r.page_table, kv->max_pages, kv->ps, kv->page_stride, hd, r.N, r.B, c->rowtab, st);
+  launch_attn_rows(r.n_b, r.page_table, kv->max_pages, kv->ps, kv->page_stride, hd, r.N, r.B, r.blk, c->rowtab, st);
   int nparts = 0;
   for (int l = 0; l < cf.n_layers; ++l) {
     const BlockW& w = m->layers[l];
-    launch_rmsnorm(dt, c->x, nparts ? c->parts : nullptr, nparts, w.attn_norm, c->xn, c->mt_v, nullptr, r.M, d,
+    launch_rmsnorm(dt, c->x, nparts ? c->parts : nullptr, nparts, w.attn_norm, c->xn, r.mtiles, nullptr, r.M, d,
                    cf.rms_eps, 1, nullptr, 0, 0, st);
     char* kbase = (char*)kv->pool + (size_t)l * kv->layer_stride * m->es;
     char* vbase = kbase + (size_t)H * kv->ps * hd * m->es;
@@ -386,7 +389,7 @@ void verify_layers(chimera_ctx* c, const VerifyRows& r, hipStream_t st, bool tim
     e.rsin = m->rsin;
     e.H = H;
     e.hd = hd;
-    g.run(c->xn, c->mt_v, r.M, w.wqkv, 3 * hdim, d, e);
+    g.run(c->xn, r.mtiles, r.M, w.wqkv, 3 * hdim, d, e);
 
     TreeAttnArgs a{};
     a.q = c->q;
@@ -409,30 +412,31 @@ void verify_layers(chimera_ctx* c, const VerifyRows& r, hipStream_t st, bool tim
     a.part_ml = c->part_ml;
     a.G = c->G;
     a.out = c->attn;
-    a.o_mtiles = c->mt_v;
+    a.o_mtiles = r.mtiles;
     a.B = r.B;
     a.rowtab = c->rowtab;
+    a.blk = r.blk;
     launch_tree_attn(dt, a, st);
 
     GemmEpi eo;
     eo.kind = EPI_PARTIAL;
     eo.part = c->parts;
-    g.run(c->attn, c->mt_v, r.M, w.wo, d, hdim, eo);
-    nparts = g.splits(d, hdim);
-    launch_rmsnorm(dt, c->x, c->parts, nparts, w.ffn_norm, c->xn, c->mt_v, nullptr, r.M, d, cf.rms_eps, 1, nullptr, 0,
+    g.run(c->attn, r.mtiles, r.M, w.wo, d, hdim, eo);
+    nparts = gemm_partials(dt, r.M, d, hdim, r.mtiles);
+    launch_rmsnorm(dt, c->x, c->parts, nparts, w.ffn_norm, c->xn, r.mtiles, nullptr, r.M, d, cf.rms_eps, 1, nullptr, 0,
                    0, st);
     GemmEpi egu;
     egu.kind = EPI_SWIGLU;
     egu.out_t = c->hbuf;
-    egu.o_mtiles = c->mt_v;
-    g.run(c->xn, c->mt_v, r.M, w.wgu, 2 * F, d, egu);
+    egu.o_mtiles = r.mtiles;
+    g.run(c->xn, r.mtiles, r.M, w.wgu, 2 * F, d, egu);
     GemmEpi ed;
     ed.kind = EPI_PARTIAL;
     ed.part = c->parts;
-    g.run(c->hbuf, c->mt_v, r.M, w.wdown, d, F, ed);
-    nparts = g.splits(d, F);
+    g.run(c->hbuf, r.mtiles, r.M, w.wdown, d, F, ed);
+    nparts = gemm_partials(dt, r.M, d, F, r.mtiles);
   }
-  launch_rmsnorm(dt, c->x, c->parts, nparts, m->final_norm, c->hl, c->mt_v, c->hl_rm, r.M, d, cf.rms_eps, 1, nullptr,
+  launch_rmsnorm(dt, c->x, c->parts, nparts, m->final_norm, c->hl, r.mtiles, c->hl_rm, r.M, d, cf.rms_eps, 1, nullptr,
                  0, 0, st);
 }
 
@@ -575,7 +579,7 @@ void run_draft(chimera_ctx* c, const StepState& s, hipStream_t st) {
     eo.kind = EPI_PARTIAL;
     eo.part = c->dparts;
     g.run(c->attn_c, c->mt_q, Q, m->enc.wo, d, hdim, eo);
-    launch_rmsnorm(dt, c->htri, c->dparts, g.splits(d, hdim), m->enc.ffn_norm, c->yn, c->mt_q, nullptr, Q, d,
+    launch_rmsnorm(dt, c->htri, c->dparts, gemm_partials(dt, Q, d, hdim, c->mt_q), m->enc.ffn_norm, c->yn, c->mt_q, nullptr, Q, d,
                    cf.rms_eps, 1, nullptr, 0, 0, st);
     GemmEpi egu;
     egu.kind = EPI_SWIGLU;
@@ -586,7 +590,7 @@ void run_draft(chimera_ctx* c, const StepState& s, hipStream_t st) {
     ed.kind = EPI_PARTIAL;
     ed.part = c->dparts;
     g.run(c->hc, c->mt_q, Q, m->enc.wdown, d, F, ed);
-    launch_draft_finish(dt, s, lv, c->htri, c->dparts, g.splits(d, F), c->zin, c->mt_q, st);
+    launch_draft_finish(dt, s, lv, c->htri, c->dparts, gemm_partials(dt, Q, d, F, c->mt_q), c->zin, c->mt_q, st);
     GemmEpi ea1;
     ea1.kind = EPI_SILU;
     ea1.out_t = c->ak;
@@ -603,6 +607,77 @@ void run_draft(chimera_ctx* c, const StepState& s, hipStream_t st) {
     g.run(c->ak, c->mt_q, Q, m->head_theta[k], V, d, et);
     launch_topk(z, ldz, s, lv, c->topk_v, c->topk_i, st);
   }
+}
+
+// One prefill chunk: the target layers over its rows (K/V into the pages),
+// the draft encoder's entries of the same positions, and the first token of
+// every prompt that ends in it.
+void prefill_chunk(chimera_ctx* c, const StepState& s, const PrefillChunk& ch, const PrefillEnds& ends,
+                   hipStream_t st) {
+  chimera_model* m = c->m;
+  chimera_kv* kv = c->kv;
+  const chimera_config& cf = m->cfg;
+  const int dt = m->dt, d = cf.d_model, H = cf.n_heads, hd = cf.head_dim, V = cf.vocab;
+  const int hdim = H * hd, M = ch.row0[ch.n_seg], mt = mcap(M) / 16;
+  const bool draft = c->K > 0;  // without a draft nothing reads the encoder's memory
+  const Gemm g{c, st, false};
+  int nblk = 0;
+  for (int k = 0; k < ch.n_seg; ++k) nblk += (ch.row0[k + 1] - ch.row0[k] + 63) / 64;
+  launch_prefill_rows(dt, s, m->embed, ch, c->pf_tokens, c->pf_blk, draft, c->tri_in, mt, c->d_pos, c->d_kvoff,
+                      c->d_qrow, st);
+  VerifyRows r{c->pf_tokens, M, nullptr, kv->page_table, c->chain.depth, c->chain.path, 64, 63, nblk, mt, c->pf_blk};
+  verify_layers(c, r, st, false);
+  if (draft) {
+    // target-state entries (rows [0, M)) and trigram entries (rows [M, 2M))
+    const int mt2 = mcap(2 * M) / 16;
+    GemmEpi e1;
+    e1.kind = EPI_SILU;
+    e1.out_t = c->tri_a;
+    e1.o_mtiles = mt;
+    g.run(c->tri_in, mt, M, m->tri_w1, d, 3 * d, e1);
+    GemmEpi e2;
+    e2.kind = EPI_F32;
+    e2.out_f = c->htri + (size_t)M * d;
+    e2.ldo = d;
+    g.run(c->tri_a, mt, M, m->tri_w2, d, d, e2);
+    if (c->tri_on)  // 64 positions at a time: one insertion per set and launch
+      for (int k = 0; k < ch.n_seg; ++k)
+        for (int r0 = ch.row0[k]; r0 < ch.row0[k + 1]; r0 += 64)
+          launch_tri_insert(s, c->tri, DraftLevel{0, 1, 0}, ch.seq[k], ch.p0[k] + r0 - ch.row0[k],
+                            std::min(64, ch.row0[k + 1] - r0), c->htri + (size_t)(M + r0) * d, st);
+    launch_rmsnorm(dt, c->htri, nullptr, 0, m->enc.attn_norm, c->un, mt2, nullptr, 2 * M, d, cf.rms_eps, 0, c->hl_rm, 0,
+                   M, st);
+    GemmEpi ekv;
+    ekv.kind = EPI_QKV;
+    ekv.pos = c->d_pos;
+    ekv.kvoff = c->d_kvoff;
+    ekv.qrow = c->d_qrow;
+    ekv.kbase = kv->enc_k;
+    ekv.vbase = kv->enc_v;
+    ekv.head_stride = (int64_t)kv->cap * hd;
+    ekv.qout = c->qc;
+    ekv.ldq = hdim;
+    ekv.rcos = m->rcos;
+    ekv.rsin = m->rsin;
+    ekv.H = H;
+    ekv.hd = hd;
+    g.run(c->un, mt2, 2 * M, m->enc.wqkv, 3 * hdim, d, ekv, hdim / 16, 2 * hdim / 16);
+  }
+  if (ends.n == 0) return;
+  const int mtl = mcap(ends.n) / 16;
+  launch_prefill_last(dt, s, ends, c->hl_rm, c->hl, mtl, st);
+  GemmEpi el;
+  el.kind = EPI_F32;
+  el.out_f = c->logits;
+  el.ldo = V;
+  g.run(c->hl, mtl, ends.n, m->lm_head, V, d, el);
+  if (c->typical)  // the first generated token is sampled at position n
+    for (int j = 0; j < ends.n; ++j)
+      launch_typical_stats(c->logits + (size_t)j * V, 1, V, 1, ends.seq[j], nullptr, nullptr, ends.len[j],
+                           1.f / c->temperature, c->t_seed, c->t_lse, c->t_H, c->amax + j, st);
+  else
+    launch_argmax(c->logits, ends.n, V, c->amax, st);
+  launch_prefill_finish(s, ends, c->amax, st);
 }
 
 void drop_graph(chimera_ctx* c) {
@@ -633,6 +708,9 @@ void carve_ctx(chimera_ctx* c, Arena& a) {
   const size_t es = m->es, d = cf.d_model, F = cf.d_ffn, V = cf.vocab, H = cf.n_heads, hd = cf.head_dim;
   const size_t B = c->B, K = c->K, Mv = c->Mv, Md = c->Md, N = c->N, Mq = c->Mq;
   const size_t Qp = (size_t)mcap(c->Mq);
+  // prefill chunks run through the verify and draft-row buffers too
+  const size_t Mp = c->Mp, Px = std::max(Mv, Mp), Pd = std::max(Md, Mp), Pe = std::max(Md, 2 * Mp);
+  const size_t nblk_pf = Mp / 64 + B;  // attention blocks of a chunk: each sequence may end one early
   c->mt_v = (int)(Mv / 16);
   c->mt_d = (int)(Md / 16);
   c->mt_q = (int)(Qp / 16);
@@ -660,14 +738,15 @@ void carve_ctx(chimera_ctx* c, Arena& a) {
   c->pro_base = a.arr<int>(B);
   c->pro_count = a.arr<int>(B);
   c->pro_h = a.take(B * (K + 1) * d * es);
-  c->pf_n = a.arr<int>(1);
-  c->pf_tokens = a.arr<int>(64);
-  c->x = a.arr<float>(Mv * d);
-  c->xn = a.take(Mv * d * es);
-  c->q = a.take(Mv * d * es);
-  c->attn = a.take(Mv * d * es);
-  c->hbuf = a.take(Mv * F * es);
-  c->parts = a.arr<float>(8 * Mv * d);
+  c->pf_tokens = a.arr<int>(Mp);
+  c->pf_blk = a.arr<PrefillBlock>(nblk_pf);
+  c->x = a.arr<float>(Px * d);
+  c->xn = a.take(Px * d * es);
+  c->q = a.take(Px * d * es);
+  c->attn = a.take(Px * d * es);
+  c->hbuf = a.take(Px * F * es);
+  const size_t max_parts = std::max(gemm_pick_splits((int)d, (int)(H * hd), m->dt), gemm_pick_splits((int)d, (int)F, m->dt));
+  c->parts = a.arr<float>(max_parts * Px * d);
   // split-K scratch: the largest splits * M * N_full over the launches this
   // context makes (partials are indexed with the full packed width)
   size_t scr = 1;
@@ -676,7 +755,7 @@ void carve_ctx(chimera_ctx* c, Arena& a) {
     if (s > 1) scr = std::max(scr, (size_t)s * M * (size_t)n_full);
   };
   const int hdim = (int)(H * hd);
-  for (size_t M : {Mv, Md, Qp, (size_t)128}) {
+  for (size_t M : {Px, Pe, Qp, (size_t)128}) {
     need(M, 3 * hdim, 3 * hdim, (int)d);
     need(M, 2 * hdim, 3 * hdim, (int)d);
     need(M, 2 * (int)F, 2 * (int)F, (int)d);
@@ -688,28 +767,28 @@ void carve_ctx(chimera_ctx* c, Arena& a) {
   c->scratch = a.arr<float>(scr);
   c->logits = a.arr<float>(Mv * V);
   c->amax = a.arr<int>(Mv);
-  c->hl = a.take(Mv * d * es);
-  c->hl_rm = a.take(Mv * d * es);
-  const size_t qrows = std::max(B * N, (size_t)64);
-  c->part_o = a.arr<float>(qrows * H * c->G * hd);
-  c->part_ml = a.arr<float>(qrows * H * c->G * 2);
-  c->rowtab = a.arr<int64_t>(B * TREE_ATTN_TAIL_ROWS);
+  c->hl = a.take(Px * d * es);
+  c->hl_rm = a.take(Px * d * es);
+  const size_t part_rows = std::max(B * N * c->G, Mp);  // one partial per group (decode) or query (prefill)
+  c->part_o = a.arr<float>(part_rows * H * hd);
+  c->part_ml = a.arr<float>(part_rows * H * 2);
+  c->rowtab = a.arr<int64_t>(std::max(B, nblk_pf) * TREE_ATTN_TAIL_ROWS);
   c->t_lse = a.arr<double>(Mv);
   c->t_H = a.arr<double>(Mv);
   c->t_sample = a.arr<int>(Mv);
   c->tri.hit = a.arr<int>(Md);
   c->tri.miss = a.arr<int>(1);
   c->tri.stats = a.arr<unsigned long long>(2);
-  c->v_pos = a.arr<int>(Mv);
-  c->v_kvoff = a.arr<int64_t>(Mv);
-  c->v_qrow = a.arr<int>(Mv);
-  c->tri_in = a.take(Md * 3 * d * es);
-  c->tri_a = a.take(Md * d * es);
-  c->htri = a.arr<float>(Md * d);
-  c->un = a.take(Md * d * es);
-  c->d_pos = a.arr<int>(Md);
-  c->d_kvoff = a.arr<int64_t>(Md);
-  c->d_qrow = a.arr<int>(Md);
+  c->v_pos = a.arr<int>(Px);
+  c->v_kvoff = a.arr<int64_t>(Px);
+  c->v_qrow = a.arr<int>(Px);
+  c->tri_in = a.take(Pd * 3 * d * es);
+  c->tri_a = a.take(Pd * d * es);
+  c->htri = a.arr<float>(Pe * d);
+  c->un = a.take(Pe * d * es);
+  c->d_pos = a.arr<int>(Pe);
+  c->d_kvoff = a.arr<int64_t>(Pe);
+  c->d_qrow = a.arr<int>(Pe);
   c->qc = a.take(Md * d * es);
   c->attn_c = a.take(Qp * d * es);
   c->yn = a.take(Qp * d * es);
@@ -787,6 +866,10 @@ void ctx_dims(chimera_ctx* c) {
   // drafted nodes (branch-conditioned drafting), fewer than N per sequence
   c->Mq = c->B * std::max(c->N - 1, 1);
   c->Md = mcap(std::max({c->B * (2 * (c->K + 1) + 1), c->Mq, 128}));
+  // rows of a prefill chunk: enough that a chunk's GEMMs fill the chip (8 row
+  // blocks of 256; a 4096-token prompt at 7B width streams the weights twice
+  // instead of 64 times), no more than the context can hold
+  c->Mp = (int)std::min<int64_t>(PREFILL_ROWS, ((int64_t)c->B * c->kv->max_len + 127) / 128 * 128);
   c->G = tree_attn_groups(c->kv->max_len);
   c->tok_stride = c->kv->max_len + 8;
   c->nblk_enc = (2 * c->kv->cap + cf.n_draft_heads + 1 + 255) / 256;
@@ -1140,70 +1223,41 @@ chimera_status chimera_prefill(chimera_model* m, chimera_kv* kv, chimera_ctx* ct
     ctx->batch = batch;
     drop_graph(ctx);
     StepState s = make_state(ctx);
-    const int dt = m->dt, d = cf.d_model, H = cf.n_heads, hd = cf.head_dim, V = cf.vocab;
-    const int hdim = H * hd;
-    const Gemm g{ctx, st, false};
     off = 0;
     for (int b = 0; b < batch; ++b) {
-      const int n = lens[b];
-      HIPCK(hipMemcpyAsync(ctx->tok + (size_t)b * ctx->tok_stride, tokens + off, sizeof(int) * n,
+      HIPCK(hipMemcpyAsync(ctx->tok + (size_t)b * ctx->tok_stride, tokens + off, sizeof(int) * lens[b],
                            hipMemcpyHostToDevice, st));
-      off += n;
-      for (int p0 = 0; p0 < n; p0 += 64) {
-        const int M = std::min(64, n - p0);
-        launch_prefill_rows(dt, s, m->embed, b, p0, M, ctx->pf_tokens, ctx->tri_in, ctx->mt_d, ctx->d_pos,
-                            ctx->d_kvoff, ctx->d_qrow, ctx->pf_n, st);
-        VerifyRows r{ctx->pf_tokens, M, ctx->pf_n, kv->page_table + (size_t)b * kv->max_pages,
-                     ctx->chain.depth, ctx->chain.path, M, M - 1, 1};
-        verify_layers(ctx, r, st, false);
-        // draft memory: target-state entries (rows [0, M)) and trigram entries (rows [M, 2M))
-        GemmEpi e1;
-        e1.kind = EPI_SILU;
-        e1.out_t = ctx->tri_a;
-        e1.o_mtiles = ctx->mt_d;
-        g.run(ctx->tri_in, ctx->mt_d, M, m->tri_w1, d, 3 * d, e1);
-        GemmEpi e2;
-        e2.kind = EPI_F32;
-        e2.out_f = ctx->htri + (size_t)M * d;
-        e2.ldo = d;
-        g.run(ctx->tri_a, ctx->mt_d, M, m->tri_w2, d, d, e2);
-        if (ctx->tri_on) launch_tri_insert(s, ctx->tri, DraftLevel{0, 1, 0}, b, p0, M, ctx->htri + (size_t)M * d, st);
-        launch_rmsnorm(dt, ctx->htri, nullptr, 0, m->enc.attn_norm, ctx->un, ctx->mt_d, nullptr, 2 * M, d, cf.rms_eps,
-                       0, ctx->hl_rm, 0, M, st);
-        GemmEpi ekv;
-        ekv.kind = EPI_QKV;
-        ekv.pos = ctx->d_pos;
-        ekv.kvoff = ctx->d_kvoff;
-        ekv.qrow = ctx->d_qrow;
-        ekv.kbase = kv->enc_k;
-        ekv.vbase = kv->enc_v;
-        ekv.head_stride = (int64_t)kv->cap * hd;
-        ekv.qout = ctx->qc;
-        ekv.ldq = hdim;
-        ekv.rcos = m->rcos;
-        ekv.rsin = m->rsin;
-        ekv.H = H;
-        ekv.hd = hd;
-        g.run(ctx->un, ctx->mt_d, 2 * M, m->enc.wqkv, 3 * hdim, d, ekv, hdim / 16, 2 * hdim / 16);
-        if (p0 + M == n) {
-          GemmEpi el;
-          el.kind = EPI_F32;
-          el.out_f = ctx->logits;
-          el.ldo = V;
-          g.run(ctx->hl, ctx->mt_v, M, m->lm_head, V, d, el);
-          if (ctx->typical)  // the first generated token is sampled at position n
-            launch_typical_stats(ctx->logits + (size_t)(M - 1) * V, 1, V, 1, b, nullptr, nullptr, n,
-                                 1.f / ctx->temperature, ctx->t_seed, ctx->t_lse, ctx->t_H, ctx->amax, st);
-          else
-            launch_argmax(ctx->logits + (size_t)(M - 1) * V, 1, V, ctx->amax, st);
-          const char* last = (const char*)ctx->hl_rm + (size_t)(M - 1) * d * m->es;
-          launch_prefill_finish(dt, s, b, n, ctx->amax, last, st);
-        }
+      off += lens[b];
+    }
+    // the prompts' tokens back to back, cut into chunks of up to Mp rows; a
+    // prompt is only cut at a multiple of 64 positions
+    int b = 0, p = 0;
+    while (b < batch) {
+      PrefillChunk c{};
+      PrefillEnds ends{};
+      while (b < batch) {
+        const int room = ctx->Mp - c.row0[c.n_seg];
+        int take = std::min(lens[b] - p, room);
+        if (take < lens[b] - p) take = take / 64 * 64;
+        if (take == 0) break;
+        c.seq[c.n_seg] = b;
+        c.p0[c.n_seg] = p;
+        c.row0[c.n_seg + 1] = c.row0[c.n_seg] + take;
+        ++c.n_seg;
+        p += take;
+        if (p < lens[b]) break;
+        ends.row[ends.n] = c.row0[c.n_seg] - 1;
+        ends.seq[ends.n] = b;
+        ends.len[ends.n] = p;
+        ++ends.n;
+        ++b;
+        p = 0;
       }
+      prefill_chunk(ctx, s, c, ends, st);
     }
     HIPCK(hipGetLastError());
     sync_or_poison(ctx, st);
-    for (int b = 0; b < batch; ++b) {
+    for (b = 0; b < batch; ++b) {
       int t = 0;
       HIPCK(hipMemcpy(&t, ctx->tok + (size_t)b * ctx->tok_stride + lens[b], sizeof(int), hipMemcpyDeviceToHost));
       first_tokens[b] = t;
@@ -1252,7 +1306,7 @@ void enqueue_step(chimera_ctx* ctx, hipStream_t st) {
     launch_tree_setup(s, q);
     const int M = ctx->batch * ctx->N;
     VerifyRows r{ctx->tree_tok, M, ctx->n, kv->page_table, ctx->tree.depth, ctx->tree.path, ctx->N, ctx->D,
-                 ctx->batch};
+                 ctx->batch, ctx->mt_v, nullptr};
     verify_layers(ctx, r, q, true);
     GemmEpi el;
     el.kind = EPI_F32;

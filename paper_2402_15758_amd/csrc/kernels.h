@@ -60,6 +60,15 @@ struct GemmShape {
 // consumers of split-K partials load them all at once).
 constexpr int GEMM_MAX_SPLITS = 8;
 int gemm_pick_splits(int n_cols, int K, int dtype);
+// Partials [parts][M][N] that an EPI_PARTIAL launch writes: its slices, or 1
+// where a launch of many rows adds them (in slice order) itself.
+int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles);
+// Launches of many rows (kernels_gemm_wide.hip, bf16): the same sums on 2-D
+// output tiles.  sums_slices: the launch applies its epilogue to the whole
+// sum; otherwise a split launch writes one partial per slice.
+bool gemm_wide_takes(int dtype, int M, int K, int x_mtiles);
+bool gemm_wide_sums_slices(int M, int nbc, int kind);
+void launch_gemm_wide(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb);
 // ev_start / ev_stop (optional): recorded by the dispatch of the GEMM's
 // first and last kernel (hipExtLaunchKernel), i.e. the kernel execution span.
 void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start = nullptr,
@@ -92,6 +101,11 @@ inline int tree_attn_groups(int max_len) {
   if (chunks <= TREE_ATTN_NEAR_CHUNKS) return (chunks + 1) / 2;
   return TREE_ATTN_NEAR_CHUNKS / 2 + (chunks - TREE_ATTN_NEAR_CHUNKS + TREE_ATTN_FAR_GROUP - 1) / TREE_ATTN_FAR_GROUP;
 }
+// A block of up to 64 consecutive prompt positions of one sequence: rows
+// row0 .. row0 + count - 1 of the launch are positions n .. n + count - 1.
+struct PrefillBlock {
+  int row0, n, count, seq;
+};
 struct TreeAttnArgs {
   const void* q;            // [B*N][ldq] rotated queries
   int ldq;
@@ -112,6 +126,9 @@ struct TreeAttnArgs {
   int o_mtiles;
   int B;
   const int64_t* rowtab;    // [B][TREE_ATTN_TAIL_ROWS] from launch_attn_rows
+  // Prefill: B query blocks of prompt positions in place of B trees (a chain
+  // each); one partial per query, part_o [rows][H][hd], part_ml [rows][H][2].
+  const PrefillBlock* blk;  // nullptr: decode
 };
 void launch_tree_attn(int dtype, const TreeAttnArgs& a, hipStream_t st);
 // Each query reduces the keys at positions P_u - W + 1 .. P_u (W = this
@@ -126,7 +143,7 @@ constexpr int TREE_ATTN_TAIL_ROWS = TREE_ATTN_WINDOW + 64;
 // rowtab[b][rr] = page-resolved element offset (head and layer excluded) of
 // window row rr, written once per verify pass for all layers.
 void launch_attn_rows(const int* n_b, const int* page_table, int max_pages, int ps, int64_t page_stride, int hd,
-                      int N, int B, int64_t* rowtab, hipStream_t st);
+                      int N, int B, const PrefillBlock* blk, int64_t* rowtab, hipStream_t st);
 
 // Query row r = b * R + i of draft level `level` is draft-tree node
 // nodes[i] of sequence b, at trigram position n_b + level.  Its keys, in
@@ -247,14 +264,25 @@ void launch_draft_rows(int dtype, const StepState& s, const void* E, const Draft
 // parts [n_parts][B R][d]
 void launch_draft_finish(int dtype, const StepState& s, const DraftLevel& lv, const float* x, const float* parts,
                          int n_parts, void* zin, int z_mtiles, hipStream_t st);
-// Prefill chunk rows: positions p0 .. p0+M-1 of sequence b; writes verify
-// descriptors (pos, kvoff through the page table, qrow), the token list,
-// trigram inputs for the same positions and the encoder descriptors of the
-// target-state rows [0, M) and trigram rows [M, 2M).
-void launch_prefill_rows(int dtype, const StepState& s, const void* E, int b, int p0, int M, int* tokens_out,
-                         void* tri_in, int tri_mtiles, int* enc_pos, int64_t* enc_kvoff, int* enc_qrow, int* pf_n,
-                         hipStream_t st);
-// Prefill end: pending token, h_last, committed length and tokens.
+// A prefill chunk: rows row0[k] .. row0[k + 1] - 1 are positions p0[k], p0[k]
+// + 1, ... of sequence seq[k].  p0 is a multiple of 64.
+constexpr int PREFILL_SEGS = 64;  // the largest batch
+struct PrefillChunk {
+  int n_seg;
+  int row0[PREFILL_SEGS + 1], seq[PREFILL_SEGS], p0[PREFILL_SEGS];
+};
+// Prompts that end in a chunk: the row of the last token, sequence, length.
+struct PrefillEnds {
+  int n;
+  int row[PREFILL_SEGS], seq[PREFILL_SEGS], len[PREFILL_SEGS];
+};
+// Rows of a prefill chunk (M in all): verify descriptors (pos, kvoff through
+// the page table, qrow), the token list and the attention blocks; with draft
+// != 0 also the trigram inputs of the same positions and the encoder
+// descriptors of the target-state rows [0, M) and trigram rows [M, 2M).
+void launch_prefill_rows(int dtype, const StepState& s, const void* E, const PrefillChunk& c, int* tokens_out,
+                         PrefillBlock* blk, int draft, void* tri_in, int tri_mtiles, int* enc_pos, int64_t* enc_kvoff,
+                         int* enc_qrow, hipStream_t st);
 // ---- trigram lookup cache (exact memoization of the trigram encoder) -------
 // Set-associative with TRI_WAYS ways and least-recently-used replacement.
 // Key of the trigram ending at position p: token ids + 1 of positions p-2,
@@ -279,8 +307,11 @@ void launch_tri_lookup(const StepState& s, const TriCache& c, const DraftLevel& 
 void launch_tri_insert(const StepState& s, const TriCache& c, const DraftLevel& lv, int b, int p0, int prefill_M,
                        const float* vals, hipStream_t st);
 
-void launch_prefill_finish(int dtype, const StepState& s, int b, int n, const int* amax_row, const void* hl_row,
-                           hipStream_t st);
+// Prefill end: states of the last rows (row-major hl_rm) to h_last and, tiled,
+// to out; then committed length and pending token of every prompt that ended.
+void launch_prefill_last(int dtype, const StepState& s, const PrefillEnds& e, const void* hl_rm, void* out,
+                         int o_mtiles, hipStream_t st);
+void launch_prefill_finish(const StepState& s, const PrefillEnds& e, const int* first, hipStream_t st);
 
 // ---- phase timestamps -------------------------------------------------------
 // Every step writes one ring slot of STAMP_WORDS words: the device wall clock

@@ -61,14 +61,16 @@ static_assert(WIN == 16, "the window pass maps four lanes to each window key");
 // n - WIN + k (committed), entry WIN + j the slot of tree node j (position
 // n + j); entries before position 0 or past the tree are zero.
 __global__ void attn_rows_kernel(const int* __restrict__ n_b, const int* __restrict__ page_table, int max_pages,
-                                 int ps, int64_t page_stride, int hd, int N, int64_t* __restrict__ rowtab) {
+                                 int ps, int64_t page_stride, int hd, int N, const PrefillBlock* __restrict__ blk,
+                                 int64_t* __restrict__ rowtab) {
   const int b = blockIdx.x;
-  const int n = n_b[b];
+  const PrefillBlock pb = blk ? blk[b] : PrefillBlock{0, n_b[b], N, b};
+  const int n = pb.n;
   for (int rr = threadIdx.x; rr < TREE_ATTN_TAIL_ROWS; rr += blockDim.x) {
     const int p = rr < WIN ? n - WIN + rr : n + rr - WIN;
     int64_t off = 0;
-    if (p >= 0 && (rr < WIN || rr - WIN < N))
-      off = (int64_t)page_table[(int64_t)b * max_pages + p / ps] * page_stride + (int64_t)(p % ps) * hd;
+    if (p >= 0 && (rr < WIN || rr - WIN < pb.count))
+      off = (int64_t)page_table[(int64_t)pb.seq * max_pages + p / ps] * page_stride + (int64_t)(p % ps) * hd;
     rowtab[(int64_t)b * TREE_ATTN_TAIL_ROWS + rr] = off;
   }
 }
@@ -76,11 +78,20 @@ __global__ void attn_rows_kernel(const int* __restrict__ n_b, const int* __restr
 // ---------------------------------------------------------------------------
 // Shared pass: grid (group slots, H, B), 4 waves; wave w owns queries
 // 16w .. 16w+15 as MFMA columns.  S^T = K Q^T, then O^T += V^T P^T.
+//
+// Prefill (PF): grid (H, 1, query blocks), blocks of up to 64 consecutive
+// prompt positions.  A workgroup walks all chunks its block sees and folds
+// each group's (m, l, O) into the running one at the group's end -- the same
+// values in the same order as the window pass folds them -- so one partial
+// per query leaves the kernel instead of one per group (at a 4096-token
+// context 21 MB a 64-row chunk of prompt and layer, written and read back).
 // ---------------------------------------------------------------------------
-template <typename T, int HD>
-// Three waves per SIMD (168 VGPRs or fewer): the pass is bound by the issue
-// of its per-chunk VALU and MFMA chains, so occupancy is what hides them.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) void tree_attn_shared(const TreeAttnArgs a) {
+// Decode keeps three waves per SIMD (168 VGPRs or fewer): the pass is bound by
+// the issue of its per-chunk VALU and MFMA chains, so occupancy is what hides
+// them.  Prefill needs 36 registers more for the running fold.
+template <typename T, int HD, bool PF>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PF ? 2 : 3, 8))) void tree_attn_shared(
+    const TreeAttnArgs a) {
   constexpr int VEC = ET<T>::VEC, KB = 4 * VEC;
   constexpr bool B16 = sizeof(T) == 2;
   constexpr int KP = HD + VEC;         // K row pitch (elements)
@@ -92,54 +103,70 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
   __shared__ __attribute__((aligned(16))) T Ks[CHUNK * KP];
   __shared__ __attribute__((aligned(16))) T Vt[B16 ? CHUNK * VRP : HD * VP];
 
-  __shared__ int64_t pbase[GMAX * CHUNK];  // element offset of each staged key's row
-  const int grp = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
+  __shared__ int64_t pbase[PF ? 1 : GMAX * CHUNK];  // element offset of each staged key's row
+  // decode: one group of one sequence; prefill: every group of one query block
+  const int grp = PF ? 0 : blockIdx.x, h = PF ? blockIdx.x : blockIdx.y;
+  const int b = PF ? gridDim.z - 1 - blockIdx.z : blockIdx.z;  // later blocks see more keys: first
+  const PrefillBlock pb = PF ? a.blk[b] : PrefillBlock{};
+  const int N = PF ? pb.count : a.N, D = PF ? pb.count - 1 : a.D;
+  const int row0 = PF ? pb.row0 : b * a.N;
+  const int* ptab = a.page_table + (int64_t)(PF ? pb.seq : b) * a.max_pages;
   // wave-uniform wave index: the MFMAs below sit under wave-level branches only
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 4, c16 = lane & 15;
   const int u = 16 * wave + c16;
-  const bool wave_on = 16 * wave < a.N;
-  const bool valid_u = u < a.N;
+  const bool wave_on = 16 * wave < N;
+  const bool valid_u = u < N;
   const int uu = valid_u ? u : 0;
   // independent loads first: the queries' fragments, their depth, n
   int4 qf[HD / KB];
   if (wave_on) {
-    const T* qrow = (const T*)a.q + (int64_t)(b * a.N + uu) * a.ldq + h * HD + g * VEC;
+    const T* qrow = (const T*)a.q + (int64_t)(row0 + uu) * a.ldq + h * HD + g * VEC;
 #pragma unroll
     for (int ks = 0; ks < HD / KB; ++ks) qf[ks] = ld16(qrow + ks * KB);
   }
-  const int dep_u = a.depth[uu];
-  const int n = a.n_b[b];
+  const int dep_u = PF ? uu : a.depth[uu];
+  const int n = PF ? pb.n : a.n_b[b];
   // the group's page ids need no n: load them with it
   const int c_begin = group_first_chunk(grp);
   const int nch = group_chunks(grp);
   constexpr int PB = (GMAX * CHUNK + 255) / 256;
   int pg[PB];
+  if constexpr (!PF) {
 #pragma unroll
-  for (int t = 0; t < PB; ++t) {
-    const int i = tid + 256 * t;
-    const int pi = (c_begin * CHUNK + i) / a.ps;
-    pg[t] = (i < nch * CHUNK && pi < a.max_pages) ? a.page_table[(int64_t)b * a.max_pages + pi] : 0;
+    for (int t = 0; t < PB; ++t) {
+      const int i = tid + 256 * t;
+      const int pi = (c_begin * CHUNK + i) / a.ps;
+      pg[t] = (i < nch * CHUNK && pi < a.max_pages) ? ptab[pi] : 0;
+    }
   }
-  const int maxk = n + a.D - WIN;        // last position any query treats as shared
+  const int maxk = n + D - WIN;          // last position any query treats as shared
   if (maxk < 0 || c_begin > maxk / CHUNK) return;
-  const int c_end = min(c_begin + nch - 1, maxk / CHUNK);
+  const int c_end = PF ? maxk / CHUNK : min(c_begin + nch - 1, maxk / CHUNK);
   const int lim_u = n + dep_u - WIN;    // query u's last shared position
   // rows past the ones written so far (positions >= n + N) may hold
   // anything: they are staged as zeros, so masked keys add exact zeros
-  const int wlim = n + a.N;
+  const int wlim = n + N;
+  if constexpr (!PF) {
 #pragma unroll
-  for (int t = 0; t < PB; ++t) {
-    const int i = tid + 256 * t;
-    const int p = c_begin * CHUNK + i;
-    if (i < nch * CHUNK) pbase[i] = (int64_t)pg[t] * a.page_stride + ((int64_t)h * a.ps + p % a.ps) * HD;
+    for (int t = 0; t < PB; ++t) {
+      const int i = tid + 256 * t;
+      const int p = c_begin * CHUNK + i;
+      if (i < nch * CHUNK) pbase[i] = (int64_t)pg[t] * a.page_stride + ((int64_t)h * a.ps + p % a.ps) * HD;
+    }
+    __syncthreads();
   }
-  __syncthreads();
   float m = -CH_INF, l = 0.f;
+  float fm = -CH_INF, fl = 0.f;  // prefill: the groups folded so far
+  f32x4 fo[PF ? HD / 16 : 1];
   const float scale2 = a.scale * LOG2E;
   f32x4 o[HD / 16];
 #pragma unroll
   for (int db = 0; db < HD / 16; ++db) o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  if constexpr (PF) {
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db) fo[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  }
 
   const T* kpool = (const T*)a.kpool;
   const T* vpool = (const T*)a.vpool;
@@ -153,16 +180,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
   constexpr int PARTS = HD / VEC;
   auto v_key = [](int idx) { return B16 ? idx / PARTS : idx % CHUNK; };
   auto v_part = [](int idx) { return B16 ? idx % PARTS : idx / CHUNK; };
+  // prefill: each thread keeps the page ids of its own rows, one chunk ahead
+  // of the rows themselves, so a row load never waits for its page id
+  int kpg[PF ? PER : 1], vpg[PF ? PER : 1];
+  auto load_pages = [&](int c) {
+    if constexpr (PF) {
+#pragma unroll
+      for (int t = 0; t < PER; ++t) {
+        const int idx = tid + 256 * t;
+        kpg[t] = ptab[min((c * CHUNK + idx / PARTS) / a.ps, a.max_pages - 1)];
+        vpg[t] = B16 ? kpg[t] : ptab[min((c * CHUNK + v_key(idx)) / a.ps, a.max_pages - 1)];
+      }
+    }
+  };
   auto load_chunk = [&](int c) {
 #pragma unroll
     for (int t = 0; t < PER; ++t) {
       const int idx = tid + 256 * t;
       const int kk = idx / PARTS, kp = idx % PARTS;
-      kreg[t] = ld16(kpool + pbase[(c - c_begin) * CHUNK + kk] + kp * VEC);
-      vreg[t] = ld16(vpool + pbase[(c - c_begin) * CHUNK + v_key(idx)] + v_part(idx) * VEC);
+      if constexpr (PF) {
+        const int kpos = c * CHUNK + kk, vpos = c * CHUNK + v_key(idx);
+        const int64_t ko = (int64_t)kpg[t] * a.page_stride + ((int64_t)h * a.ps + kpos % a.ps) * HD;
+        const int64_t vo = (int64_t)vpg[t] * a.page_stride + ((int64_t)h * a.ps + vpos % a.ps) * HD;
+        kreg[t] = ld16(kpool + ko + kp * VEC);
+        vreg[t] = ld16(vpool + vo + v_part(idx) * VEC);
+      } else {
+        kreg[t] = ld16(kpool + pbase[(c - c_begin) * CHUNK + kk] + kp * VEC);
+        vreg[t] = ld16(vpool + pbase[(c - c_begin) * CHUNK + v_key(idx)] + v_part(idx) * VEC);
+      }
     }
   };
+  load_pages(c_begin);
   load_chunk(c_begin);
+  load_pages(c_begin + 1);
   for (int c = c_begin; c <= c_end; ++c) {
     __syncthreads();
     // every row of the chunk written so far: no zero staging (uniform)
@@ -183,7 +233,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
       }
     }
     __syncthreads();
-    if (c < c_end) load_chunk(c + 1);
+    if (c < c_end) {
+      load_chunk(c + 1);
+      load_pages(c + 2);
+    }
     if (!wave_on) continue;
 
     f32x4 s[4];
@@ -310,8 +363,35 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
           o[db] = mfma_kb<T>(ld16(&Vt[(16 * db + c16) * VP + 16 * kb + 4 * g]), bfrag, o[db]);
       }
     }
+    if constexpr (PF) {
+      // end of a group: fold it (the window pass's arithmetic) and start anew
+      if ((c == c_end || group_of_chunk(c + 1) != group_of_chunk(c)) && m != -CH_INF) {
+        const float mn2 = fmaxf(fm, m);
+        const float a1 = exp2_diff(fm, mn2), a2 = __builtin_amdgcn_exp2f(m - mn2);
+        fl = fl * a1 + l * a2;
+#pragma unroll
+        for (int db = 0; db < HD / 16; ++db) {
+          fo[db] = fo[db] * a1 + o[db] * a2;
+          o[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        fm = mn2;
+        m = -CH_INF;
+        l = 0.f;
+      }
+    }
   }
   if (!valid_u) return;
+  if constexpr (PF) {
+    const int64_t slot = (int64_t)(row0 + u) * a.H + h;
+    float* po = a.part_o + slot * HD;
+#pragma unroll
+    for (int db = 0; db < HD / 16; ++db) *reinterpret_cast<f32x4*>(po + 16 * db + 4 * g) = fo[db];
+    if (g == 0) {
+      a.part_ml[slot * 2] = fm;
+      a.part_ml[slot * 2 + 1] = fl;
+    }
+    return;
+  }
   const int64_t slot = (((int64_t)b * a.H + h) * a.G + grp) * a.N + u;
   float* po = a.part_o + slot * HD;
 #pragma unroll
@@ -338,35 +418,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3, 8))) voi
 // slot of u's ancestor at depth p - n from n on.  Keys before position 0
 // read u's own slot and add exact zeros.
 // ---------------------------------------------------------------------------
-template <typename T, int HD>
+// Prefill (PF): grid (ceil(H / 4), 64, query blocks); one folded partial.
+template <typename T, int HD, bool PF>
 __global__ __launch_bounds__(256) void tree_attn_window(const TreeAttnArgs a) {
   constexpr int VEC = ET<T>::VEC;
   constexpr int DPL = HD / 64;   // output dims per lane
   constexpr int LPK = 64 / WIN;  // lanes per window key
   constexpr int DPK = HD / LPK;  // score dims per lane
   constexpr int NQ = DPK / VEC;  // 16-byte loads per lane and row
-  constexpr int BATCH = 8;       // group partials loaded per round trip
+  constexpr int BATCH = PF ? 1 : 8;  // group partials loaded per round trip
   static_assert(NQ >= 1 && DPK % VEC == 0, "window layout");
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = 4 * blockIdx.x + wave, u = blockIdx.y, b = blockIdx.z;
   if (h >= a.H) return;  // wave-uniform
+  const PrefillBlock pb = PF ? a.blk[b] : PrefillBlock{};
+  if (PF && u >= pb.count) return;
+  const int row = PF ? pb.row0 + u : b * a.N + u;
   const int kw = lane / LPK, sub = lane % LPK;
   // 1. loads that need nothing
-  const int n = a.n_b[b];
-  const int dep = a.depth[u];
-  const int pth = a.path[u * 64 + lane];  // node at depth `lane` on u's path
+  const int n = PF ? pb.n : a.n_b[b];
+  const int dep = PF ? u : a.depth[u];
+  const int pth = PF ? lane : a.path[u * 64 + lane];  // node at depth `lane` on u's path
   const int64_t* rt = a.rowtab + (int64_t)b * TREE_ATTN_TAIL_ROWS;
   const long long r_lo = rt[lane];                           // entries 0 .. 63
   const long long r_hi = rt[64 + (lane & (TREE_ATTN_TAIL_ROWS - 64 - 1))];  // entries 64 ..
   int4 qv[NQ];
   {
-    const T* qrow = (const T*)a.q + (int64_t)(b * a.N + u) * a.ldq + h * HD + sub * DPK;
+    const T* qrow = (const T*)a.q + (int64_t)row * a.ldq + h * HD + sub * DPK;
 #pragma unroll
     for (int i = 0; i < NQ; ++i) qv[i] = ld16(qrow + i * VEC);
   }
   float bm[BATCH], bl[BATCH], bo[BATCH][DPL];
   // this (sequence, head, query)'s partials: group g at slot base + g * N
-  const int64_t slot0 = ((int64_t)b * a.H + h) * a.G * a.N + u;
+  const int64_t slot0 = PF ? (int64_t)row * a.H + h : ((int64_t)b * a.H + h) * a.G * a.N + u;
   const float* pml = a.part_ml + slot0 * 2;
   const float* po = a.part_o + slot0 * HD + DPL * lane;
   auto load_batch = [&](int g0, int lim_g) {
@@ -386,7 +470,7 @@ __global__ __launch_bounds__(256) void tree_attn_window(const TreeAttnArgs a) {
     }
   };
   // slots past this step's groups are read but never folded
-  load_batch(0, a.G);
+  load_batch(0, PF ? 1 : a.G);
 
   // 2. the window rows
   const int Pu = n + dep;
@@ -414,7 +498,7 @@ __global__ __launch_bounds__(256) void tree_attn_window(const TreeAttnArgs a) {
   }
   // while they are in flight: fold the group partials in group order
   const int lim = Pu - WIN;
-  const int ngrp = lim >= 0 ? group_of_chunk(lim / CHUNK) + 1 : 0;
+  const int ngrp = lim < 0 ? 0 : (PF ? 1 : group_of_chunk(lim / CHUNK) + 1);
   float m = -CH_INF, l = 0.f, o[DPL];
 #pragma unroll
   for (int d = 0; d < DPL; ++d) o[d] = 0.f;
@@ -461,13 +545,18 @@ __global__ __launch_bounds__(256) void tree_attn_window(const TreeAttnArgs a) {
     for (int d = 0; d < DPL; ++d) o[d] = fmaf(pk, ET<T>::to_f(vv[k][d]), o[d]);
   }
 #pragma unroll
-  for (int d = 0; d < DPL; ++d) store_tiled<T>((T*)a.out, a.o_mtiles, b * a.N + u, h * HD + DPL * lane + d, o[d] / l);
+  for (int d = 0; d < DPL; ++d) store_tiled<T>((T*)a.out, a.o_mtiles, row, h * HD + DPL * lane + d, o[d] / l);
 }
 
 template <typename T, int HD>
 void tree_attn_go(const TreeAttnArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((tree_attn_shared<T, HD>), dim3(a.G, a.H, a.B), dim3(256), 0, st, a);
-  hipLaunchKernelGGL((tree_attn_window<T, HD>), dim3((a.H + 3) / 4, a.N, a.B), dim3(256), 0, st, a);
+  if (a.blk != nullptr) {
+    hipLaunchKernelGGL((tree_attn_shared<T, HD, true>), dim3(a.H, 1, a.B), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((tree_attn_window<T, HD, true>), dim3((a.H + 3) / 4, 64, a.B), dim3(256), 0, st, a);
+    return;
+  }
+  hipLaunchKernelGGL((tree_attn_shared<T, HD, false>), dim3(a.G, a.H, a.B), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((tree_attn_window<T, HD, false>), dim3((a.H + 3) / 4, a.N, a.B), dim3(256), 0, st, a);
 }
 
 // ---------------------------------------------------------------------------
@@ -628,9 +717,9 @@ void enc_attn_go(const EncAttnArgs& a, hipStream_t st) {
 }  // namespace
 
 void launch_attn_rows(const int* n_b, const int* page_table, int max_pages, int ps, int64_t page_stride, int hd,
-                      int N, int B, int64_t* rowtab, hipStream_t st) {
+                      int N, int B, const PrefillBlock* blk, int64_t* rowtab, hipStream_t st) {
   hipLaunchKernelGGL(attn_rows_kernel, dim3(B), dim3(TREE_ATTN_TAIL_ROWS), 0, st, n_b, page_table, max_pages, ps,
-                     page_stride, hd, N, rowtab);
+                     page_stride, hd, N, blk, rowtab);
 }
 
 void launch_tree_attn(int dtype, const TreeAttnArgs& a, hipStream_t st) {

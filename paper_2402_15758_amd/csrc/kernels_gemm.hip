@@ -25,6 +25,7 @@
 #include <algorithm>
 
 #include "common.h"
+#include "gemm_epilogue.h"
 #include "kernels.h"
 
 // The GEMM kernels take GemmShape and GemmEpi by value: a plain block of
@@ -34,7 +35,6 @@ static_assert(alignof(GemmShape) <= 8 && alignof(GemmEpi) <= 8, "GEMM kernel-arg
 
 namespace {
 
-constexpr int NB = 4;        // 16-column blocks per weight-layout group
 constexpr int CB_MAX = 8;    // column blocks per workgroup, upper bound
 constexpr int RED_TILES = 32;  // 16x16 output tiles per wave in one LDS reduction round (4 x 32 KiB)
 constexpr int GEMM_WGS = 256;  // one workgroup per CU per reduction slice
@@ -86,111 +86,6 @@ __global__ void repack_kernel(const T* __restrict__ s0, const T* __restrict__ s1
   T* d = dst + ((((int64_t)(c / NB) * kblocks + kb) * NB + c % NB) * 64 + lane) * VEC;
 #pragma unroll
   for (int e = 0; e < VEC; ++e) d[e] = src[(int64_t)(k0 + e) * n_src + col];
-}
-
-// ---------------------------------------------------------------------------
-// Epilogue of one output element: v is packed column 16 blk + c16 of `row`,
-// vp the same row's value at lane column c16 ^ 8 (the other half of a rotary
-// or gate/up pair).
-// ---------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ void epi_elem(const GemmEpi& e, int kind, int N, int M, int split, int row, int blk,
-                                         int c16, float v, float vp) {
-  const int col = 16 * blk + c16;
-  if (kind == EPI_PARTIAL) {
-    e.part[((int64_t)split * M + row) * N + col] = v;
-  } else if (kind == EPI_F32) {
-    e.out_f[(int64_t)row * e.ldo + col] = v;
-  } else if (kind == EPI_T) {
-    store_tiled<T>((T*)e.out_t, e.o_mtiles, row, col, v);
-  } else if (kind == EPI_SILU) {
-    store_tiled<T>((T*)e.out_t, e.o_mtiles, row, col, silu_f(v));
-  } else if (kind == EPI_SWIGLU) {
-    if (c16 < 8) store_tiled<T>((T*)e.out_t, e.o_mtiles, row, 8 * blk + c16, silu_f(v) * vp);
-  } else if (kind == EPI_QKV) {
-    const int hd = e.hd;
-    const int blk_head = hd / 16;
-    const int sec_blks = e.H * blk_head;
-    const int sec = blk / sec_blks, rem = blk % sec_blks;
-    const int h = rem / blk_head, q = rem % blk_head;
-    if (sec < 2) {
-      const bool first = c16 < 8;
-      const int i = 8 * q + (c16 & 7);
-      const int pos = e.pos[row];
-      const float c = e.rcos[(int64_t)pos * (hd / 2) + i];
-      const float s = e.rsin[(int64_t)pos * (hd / 2) + i];
-      // first half: x1 cos - x2 sin; second half: x2 cos + x1 sin
-      const float o = first ? v * c - vp * s : v * c + vp * s;
-      const int dim = first ? i : i + hd / 2;
-      if (sec == 0) {
-        const int qr = e.qrow[row];
-        if (qr >= 0) ((T*)e.qout)[(int64_t)qr * e.ldq + h * hd + dim] = ET<T>::from_f(o);
-      } else {
-        const int64_t off = e.kvoff[row];
-        if (off >= 0) ((T*)e.kbase)[off + h * e.head_stride + dim] = ET<T>::from_f(o);
-      }
-    } else {
-      const int64_t off = e.kvoff[row];
-      if (off >= 0) ((T*)e.vbase)[off + h * e.head_stride + 16 * q + c16] = ET<T>::from_f(v);
-    }
-  }
-}
-
-// Per-row targets of the QKV epilogue, staged in LDS before the k-loop.
-struct RowMeta {
-  int64_t kvoff;  // K/V element offset (-1: skip)
-  int pos;        // rotary position
-  int qrow;       // Q output row (-1: skip)
-};
-
-// QKV epilogue of one element with its rotary cos/sin already loaded (the
-// same arithmetic as epi_elem's EPI_QKV branch).
-template <typename T>
-__device__ __forceinline__ void qkv_store(const GemmEpi& e, const RowMeta& rm, int blk, int c16, float v, float vp,
-                                          float c, float s) {
-  const int hd = e.hd;
-  const int blk_head = hd / 16;
-  const int sec_blks = e.H * blk_head;
-  const int sec = blk / sec_blks, rem = blk % sec_blks;
-  const int h = rem / blk_head, q = rem % blk_head;
-  if (sec < 2) {
-    const bool first = c16 < 8;
-    const int i = 8 * q + (c16 & 7);
-    const float o = first ? v * c - vp * s : v * c + vp * s;
-    const int dim = first ? i : i + hd / 2;
-    if (sec == 0) {
-      if (rm.qrow >= 0) ((T*)e.qout)[(int64_t)rm.qrow * e.ldq + h * hd + dim] = ET<T>::from_f(o);
-    } else if (rm.kvoff >= 0) {
-      ((T*)e.kbase)[rm.kvoff + h * e.head_stride + dim] = ET<T>::from_f(o);
-    }
-  } else if (rm.kvoff >= 0) {
-    ((T*)e.vbase)[rm.kvoff + h * e.head_stride + 16 * q + c16] = ET<T>::from_f(v);
-  }
-}
-
-// The same element's value before the store: rotated Q/K or plain V.
-__device__ __forceinline__ float qkv_value(const GemmEpi& e, int blk, int c16, float v, float vp, float c, float s) {
-  const int sec = blk / (e.H * (e.hd / 16));
-  if (sec == 2) return v;
-  return c16 < 8 ? v * c - vp * s : v * c + vp * s;
-}
-
-// 8 consecutive outputs of one row of a QKV tile as one 16-byte store: half 0
-// holds lane columns 0..7 of block blk, half 1 columns 8..15.
-template <typename T>
-__device__ __forceinline__ void qkv_store16(const GemmEpi& e, const RowMeta& rm, int blk, int half, int4 v) {
-  const int hd = e.hd;
-  const int blk_head = hd / 16;
-  const int sec_blks = e.H * blk_head;
-  const int sec = blk / sec_blks, rem = blk % sec_blks;
-  const int h = rem / blk_head, q = rem % blk_head;
-  const int dim = sec < 2 ? (half ? hd / 2 : 0) + 8 * q : 16 * q + 8 * half;
-  if (sec == 0) {
-    if (rm.qrow >= 0) *reinterpret_cast<int4*>((T*)e.qout + (int64_t)rm.qrow * e.ldq + h * hd + dim) = v;
-  } else if (rm.kvoff >= 0) {
-    T* base = (T*)(sec == 1 ? e.kbase : e.vbase);
-    *reinterpret_cast<int4*>(base + rm.kvoff + h * e.head_stride + dim) = v;
-  }
 }
 
 template <typename T>
@@ -526,7 +421,7 @@ void gemm_launch(const GemmShape& s, const GemmEpi& e, int kind, int nwg, int nb
   dim3 grid((s.M + 16 * MB - 1) / (16 * MB), nwg, s.splits);
   const int gx = (int)grid.x, gy = (int)grid.y;
   if (gx > 1 && (gy * s.splits) % GEMM_XCDS == 0) {
-    if constexpr (MB > 1) {
+    if constexpr (MB > 1 && sizeof(T) == 4) {  // bf16 launches of several row blocks go to the wide kernel
       if (ea || eb)
         hipExtLaunchKernelGGL((gemm_kernel<T, MB, CBA, true>), grid, dim3(256), 0, st, ea, eb, 0, s, e, kind, nbig, gx,
                               gy);
@@ -572,9 +467,22 @@ void gemm_mb8(const GemmShape& s, const GemmEpi& e, int kind, int nwg, int cba, 
   }
 }
 
+int gemm_blocks(const GemmShape& s) { return s.nb_count ? s.nb_count : s.N / 16; }
+
+template <typename T>
+void launch_finish(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_stop) {
+  const int64_t total = (int64_t)s.M * gemm_blocks(s) * 16;
+  const dim3 grid((unsigned)((total + 255) / 256));
+  if (ev_stop)
+    hipExtLaunchKernelGGL((gemm_finish_kernel<T>), grid, dim3(256), 0, st, nullptr, ev_stop, 0, s, e, e.kind,
+                          (const float*)e.part);
+  else
+    hipLaunchKernelGGL((gemm_finish_kernel<T>), grid, dim3(256), 0, st, s, e, e.kind, (const float*)e.part);
+}
+
 template <typename T>
 void gemm_t(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  const int nbc = s.nb_count ? s.nb_count : s.N / 16;
+  const int nbc = gemm_blocks(s);
   // workgroups per slice: GEMM_WGS / splits, at least ceil(nbc / CB_MAX),
   // at most one per column block; runs of cba or cba - 1 blocks
   int nwg = (GEMM_WGS + s.splits - 1) / s.splits;
@@ -608,15 +516,7 @@ void gemm_t(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_
     }
   } else
     gemm_mb<T, 4>(s, e, kind, nwg, cba, nbig, st, ev_start, eb);
-  if (finish) {
-    const int64_t total = (int64_t)s.M * nbc * 16;
-    const dim3 grid((unsigned)((total + 255) / 256));
-    if (ev_stop)
-      hipExtLaunchKernelGGL((gemm_finish_kernel<T>), grid, dim3(256), 0, st, nullptr, ev_stop, 0, s, e, e.kind,
-                            (const float*)e.part);
-    else
-      hipLaunchKernelGGL((gemm_finish_kernel<T>), grid, dim3(256), 0, st, s, e, e.kind, (const float*)e.part);
-  }
+  if (finish) launch_finish<T>(s, e, st, ev_stop);
 }
 
 template <typename T>
@@ -650,9 +550,28 @@ int gemm_pick_splits(int n_cols, int K, int dtype) {
   return s;
 }
 
+int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles) {
+  if (gemm_wide_takes(dtype, M, K, x_mtiles) && gemm_wide_sums_slices(M, n_cols / 16, EPI_PARTIAL)) return 1;
+  return gemm_pick_splits(n_cols, K, dtype);
+}
+
 void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start,
                  hipEvent_t ev_stop) {
   if (s.M <= 0) return;
+  if (gemm_wide_takes(dtype, s.M, s.K, s.x_mtiles)) {
+    const bool finish = s.splits > 1 && e.kind != EPI_PARTIAL && !gemm_wide_sums_slices(s.M, gemm_blocks(s), e.kind);
+    if (finish) {
+      GemmEpi p = e;
+      p.kind = EPI_PARTIAL;
+      launch_gemm_wide(s, p, st, ev_start, nullptr);
+      GemmShape f = s;
+      if (gemm_wide_sums_slices(s.M, gemm_blocks(s), EPI_PARTIAL)) f.splits = 1;  // one summed partial was written
+      launch_finish<bf16_t>(f, e, st, ev_stop);
+    } else {
+      launch_gemm_wide(s, e, st, ev_start, ev_stop);
+    }
+    return;
+  }
   if (dtype == DT_BF16)
     gemm_t<bf16_t>(s, e, st, ev_start, ev_stop);
   else

@@ -1,0 +1,470 @@
+// GEMMs of more than 128 bf16 rows (prefill chunks, wide verify batches):
+// Y = X[M][K] @ W[K][N] on 2-D output tiles, with the operands of
+// kernels_gemm.hip (both in MFMA fragment order) and its summation order, bit
+// for bit: per reduction slice four partial sums, one per residue class of the
+// k-blocks mod 4, added in class order, then the slices in slice order.
+//
+// The streaming kernel gives each of its four waves one class, so a workgroup
+// re-reads its activation rows for every run of 6 columns blocks: fine while
+// the weight stream is what is waited for, and 430-600 TFLOP/s on 2048 rows.
+// Here a workgroup owns a tile of up to 256 rows x 128 columns, its eight
+// waves 64 x 64 (two a SIMD: 64 accumulators, 64 totals and, with the slices
+// added in registers, 64 sums fit their 256 registers), and the classes run
+// one after another.  Operand tiles go from memory straight into a ring of
+// four LDS stages (global_load_lds, 1 KiB a wave: fragment order is what such
+// a load writes), so a stage costs no registers and one barrier.
+//
+// What bounds it: LDS.  A k-block of the 256 x 128 tile is 512 cycles of MFMA
+// on every SIMD and 88 KiB through LDS (64 read, 24 written).  Measured
+// against the streaming kernel, 7B shapes, us: 2048 rows QKV 477 -> 230, O
+// 153 -> 68, gate/up 620 -> 365, down 319 -> 167 (1.1 PFLOP/s); 256 rows QKV
+// 46 -> 43, O 22 -> 16, gate/up 76 -> 61, down 43 -> 34, LM head 119 -> 75.
+// More stages (6, 8) and fragments read a step ahead were no faster.
+#include <hip/hip_ext.h>
+
+#include <algorithm>
+
+#include "common.h"
+#include "gemm_epilogue.h"
+#include "kernels.h"
+
+namespace {
+
+constexpr int XCDS = 8;
+
+template <int N>
+struct Int {
+  static constexpr int value = N;
+};
+
+// s_waitcnt vmcnt(N) alone (lgkmcnt and expcnt unconstrained).
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+}
+__device__ __forceinline__ void wg_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+// 16 bytes per lane, 1 KiB per wave, straight from memory into LDS.
+__device__ __forceinline__ void dma_tile(const char* src, char* lds) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                   (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+
+// Store one 16x16 output tile (row block mb, column block blk): v in MFMA
+// layout (lane (g, c16): rows 4g .. 4g+3, column c16).  tw: 1 KiB of LDS of
+// this wave.  rm: row targets of the tile's 16 rows (QKV).
+template <typename T, int KIND>
+__device__ __forceinline__ void store_tile(const GemmShape& sh, const GemmEpi& e, int mb, int blk, f32x4 v, float* part,
+                                           float* tw, const RowMeta* rm, f32x4 cs, f32x4 sn, int lane) {
+  const int g = lane >> 4, c16 = lane & 15;
+  if constexpr (KIND == EPI_F32 || KIND == EPI_PARTIAL) {
+    float* base = KIND == EPI_F32 ? e.out_f : part;
+    const int64_t ld = KIND == EPI_F32 ? e.ldo : sh.N;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tw[(4 * g + r) * 16 + c16] = v[r];
+    __builtin_amdgcn_wave_barrier();
+    const int row = 16 * mb + (lane >> 2);
+    const float4 o = *reinterpret_cast<const float4*>(tw + (lane >> 2) * 16 + 4 * (lane & 3));
+    if (row < sh.M) *reinterpret_cast<float4*>(base + (int64_t)row * ld + 16 * blk + 4 * (lane & 3)) = o;
+    __builtin_amdgcn_wave_barrier();
+    return;
+  }
+  f32x4 vp;  // lane column c16 ^ 8
+#pragma unroll
+  for (int r = 0; r < 4; ++r) vp[r] = dpp_mov<DPP_ROR8>(v[r]);
+  if constexpr (sizeof(T) == 2 && KIND == EPI_SWIGLU) {
+    T* tt = reinterpret_cast<T*>(tw);
+    if (c16 < 8) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) tt[(4 * g + r) * 8 + c16] = ET<T>::from_f(silu_f(v[r]) * vp[r]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 16) {
+      const int row = 16 * mb + lane;
+      const int4 o = *reinterpret_cast<const int4*>(tt + lane * 8);
+      if (row < sh.M) *reinterpret_cast<int4*>((T*)e.out_t + tiled_index<T>(e.o_mtiles, row, 8 * blk)) = o;
+    }
+    __builtin_amdgcn_wave_barrier();
+  } else if constexpr (KIND == EPI_QKV) {
+    T* tt = reinterpret_cast<T*>(tw);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if constexpr (sizeof(T) == 2)
+        tt[(4 * g + r) * 16 + c16] = ET<T>::from_f(qkv_value(e, blk, c16, v[r], vp[r], cs[r], sn[r]));
+      else if (16 * mb + 4 * g + r < sh.M)
+        qkv_store<T>(e, rm[4 * g + r], blk, c16, v[r], vp[r], cs[r], sn[r]);
+    }
+    if constexpr (sizeof(T) == 2) {
+      __builtin_amdgcn_wave_barrier();
+      if (lane < 32) {
+        const int4 o = *reinterpret_cast<const int4*>(tt + (lane & 15) * 16 + 8 * (lane >> 4));
+        if (16 * mb + (lane & 15) < sh.M) qkv_store16<T>(e, rm[lane & 15], blk, lane >> 4, o);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * mb + 4 * g + r;
+      if (row < sh.M) epi_elem<T>(e, KIND, sh.N, sh.M, 0, row, blk, c16, v[r], vp[r]);
+    }
+  }
+}
+
+// Waves WM x WN, each MT 16-row tiles x CB column blocks; NS ring stages.  SL:
+// the workgroup runs all reduction slices and adds them (otherwise it runs the
+// one its place in the grid names).  AL: every class is a multiple of NS
+// k-blocks, so a class always starts at ring position 0.
+template <typename T, int KIND, int WM, int WN, int MT, int CB, int NS, bool SL, bool AL>
+__global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_kernel(const GemmShape sh, const GemmEpi e,
+                                                                                   int nrb, int ncb) {
+  constexpr int VEC = ET<T>::VEC;
+  constexpr int NW = WM * WN;
+  constexpr int TA = WM * MT, TB = WN * CB, NT = TA + TB;  // 1 KiB tiles per stage
+  constexpr int P = (NT + NW - 1) / NW;                    // of them per wave
+  static_assert(NS >= 3 && NS <= 8, "stages");
+  // one array per stage, and every use of one names it at compile time: the
+  // compiler then knows which loads a read of a stage has to wait for
+  constexpr int SB = NT * 1024;
+  __shared__ __attribute__((aligned(1024))) char s0[SB], s1[SB], s2[SB], s3[NS > 3 ? SB : 16], s4[NS > 4 ? SB : 16],
+      s5[NS > 5 ? SB : 16], s6[NS > 6 ? SB : 16], s7[NS > 7 ? SB : 16];
+  __shared__ RowMeta rm[KIND == EPI_QKV ? 16 * TA : 1];
+
+  if (sh.skip && *sh.skip == 0) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN;
+  const int kblocks = sh.K / (4 * VEC);
+  const int nbc = sh.nb_count ? sh.nb_count : sh.N / 16;
+  // column runs are dealt to the dies in contiguous ranges, row blocks fastest
+  const int zs = SL ? 1 : sh.splits;
+  const int total = nrb * ncb * zs;
+  const int xcd = blockIdx.x % XCDS, q = total / XCDS, rem = total % XCDS;
+  const int idx = xcd * q + min(xcd, rem) + (int)blockIdx.x / XCDS;
+  const int mb0 = (idx % nrb) * TA, cb0 = ((idx / nrb) % ncb) * TB, split = idx / (nrb * ncb);
+
+  if constexpr (KIND == EPI_QKV) {
+    for (int i = tid; i < 16 * TA; i += 64 * NW) {
+      const int row = 16 * mb0 + i;
+      RowMeta t{-1, 0, -1};
+      if (row < sh.M) t = RowMeta{e.kvoff[row], e.pos[row], e.qrow[row]};
+      rm[i] = t;
+    }
+  }
+  // this wave's share of a stage: tiles wave, wave + NW, ... (past the last:
+  // the last one again); rows and columns past the edge read the last tile
+  const int kps = kblocks / sh.splits;
+  const char* base[P];
+  uint32_t step[P];  // bytes between consecutive k-blocks (an operand panel is under 4 GiB)
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int t = min(wave + NW * p, NT - 1);
+    if (t < TA) {
+      step[p] = (uint32_t)sh.x_mtiles * 1024;
+      base[p] = (const char*)sh.X + (int64_t)min(mb0 + t, sh.x_mtiles - 1) * 1024;
+    } else {
+      const int c = sh.nb_off + min(cb0 + t - TA, nbc - 1);
+      step[p] = NB * 1024;
+      base[p] = (const char*)sh.W + ((int64_t)(c / NB) * kblocks * NB + c % NB) * 1024;
+    }
+    base[p] += (int64_t)(split * kps) * step[p];
+  }
+  const uint32_t lane16 = lane * 16;
+  auto issue = [&](char* buf, uint32_t kb) __attribute__((always_inline)) {
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+      dma_tile(base[p] + (kb * step[p] + lane16), buf + min(wave + NW * p, NT - 1) * 1024);
+  };
+
+  f32x4 acc[MT][CB], tot[MT][CB], sum[SL ? MT : 1][SL ? CB : 1];
+  const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  const f32x4 nzero = f32x4{-0.f, -0.f, -0.f, -0.f};  // nzero + x is x, bit for bit
+  // Loads run NS - 1 stages ahead of the sums, over the k-blocks in the order
+  // of the summation: in each slice the residue classes mod 4 one after
+  // another.  Past the end they repeat k-block 0 (nothing reads it).
+  const int slices = SL ? sh.splits : 1;
+  int lbase = 0, lcls = 0, lkb = 0;
+  const int lend = slices * kps, cls_n = min(4, kps);
+  auto next_kb = [&]() __attribute__((always_inline)) {  // no branches: it sits between a barrier and the stage's loads
+    const int kb = lbase < lend ? lbase + lkb : 0;
+    const int nk = lkb + 4, c1 = lcls + 1;
+    const bool wrap = nk >= kps, last = c1 >= cls_n;
+    lkb = wrap ? (last ? 0 : c1) : nk;
+    lcls = wrap ? (last ? 0 : c1) : lcls;
+    lbase += wrap && last ? kps : 0;
+    return (uint32_t)kb;
+  };
+  auto buf = [&](auto i) __attribute__((always_inline)) -> char* {
+    constexpr int k = decltype(i)::value % NS;
+    if constexpr (k == 0) return s0;
+    else if constexpr (k == 1) return s1;
+    else if constexpr (k == 2) return s2;
+    else if constexpr (k == 3) return s3;
+    else if constexpr (k == 4) return s4;
+    else if constexpr (k == 5) return s5;
+    else if constexpr (k == 6) return s6;
+    else return s7;
+  };
+  // one stage: its own loads have landed (NS - 2 later stages still in
+  // flight), every wave is past the stage before, whose buffer is refilled
+  auto step_k = [&](auto i) __attribute__((always_inline)) {
+    constexpr int I = decltype(i)::value;
+    wait_vm<P * (NS - 2)>();
+    wg_barrier();
+    issue(buf(Int<I + NS - 1>{}), next_kb());
+    const char* b = buf(i);
+    int4 fa[MT], fb[CB];
+#pragma unroll
+    for (int j = 0; j < CB; ++j) fb[j] = ld16(b + (TA + wn * CB + j) * 1024 + lane16);
+#pragma unroll
+    for (int k = 0; k < MT; ++k) fa[k] = ld16(b + (wm * MT + k) * 1024 + lane16);
+#pragma unroll
+    for (int k = 0; k < MT; ++k)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) acc[k][j] = mfma_kb<T>(fa[k], fb[j], acc[k][j]);
+  };
+  // the n k-blocks of one class, the first of them in ring position PH
+  auto round = [&](auto ph) __attribute__((always_inline)) {
+    constexpr int PH = decltype(ph)::value;
+    step_k(Int<PH>{});
+    step_k(Int<PH + 1>{});
+    step_k(Int<PH + 2>{});
+    if constexpr (NS > 3) step_k(Int<PH + 3>{});
+    if constexpr (NS > 4) step_k(Int<PH + 4>{});
+    if constexpr (NS > 5) step_k(Int<PH + 5>{});
+    if constexpr (NS > 6) step_k(Int<PH + 6>{});
+    if constexpr (NS > 7) step_k(Int<PH + 7>{});
+  };
+  auto run_class = [&](auto ph, int n) __attribute__((always_inline)) {
+    constexpr int PH = decltype(ph)::value;
+    int r = n / NS;
+    if constexpr (AL) {
+      for (; r > 0; --r) round(ph);
+    } else {
+      // a first round on its own: only its waits have to cover every history
+      // of the ring that leads here
+      if (r > 0) {
+        round(ph);
+        while (--r > 0) round(ph);
+      }
+      r = n % NS;
+      if (r > 0) step_k(Int<PH>{});
+      if (r > 1) step_k(Int<PH + 1>{});
+      if (NS > 3 && r > 2) step_k(Int<PH + 2>{});
+      if (NS > 4 && r > 3) step_k(Int<PH + 3>{});
+      if (NS > 5 && r > 4) step_k(Int<PH + 4>{});
+      if (NS > 6 && r > 5) step_k(Int<PH + 5>{});
+      if (NS > 7 && r > 6) step_k(Int<PH + 6>{});
+    }
+  };
+  issue(s0, next_kb());
+  issue(s1, next_kb());
+  if constexpr (NS > 3) issue(s2, next_kb());
+  if constexpr (NS > 4) issue(s3, next_kb());
+  if constexpr (NS > 5) issue(s4, next_kb());
+  if constexpr (NS > 6) issue(s5, next_kb());
+  if constexpr (NS > 7) issue(s6, next_kb());
+  int phase = 0;
+#pragma unroll 1
+  for (int sl = 0; sl < slices; ++sl) {
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < CB; ++j) tot[i][j] = nzero;
+#pragma unroll 1
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) acc[i][j] = zero;
+      const int n = (kps - c + 3) / 4;
+      if constexpr (AL) {
+        run_class(Int<0>{}, n);
+      } else {
+        if (phase == 0) run_class(Int<0>{}, n);
+        else if (phase == 1) run_class(Int<1>{}, n);
+        else if (phase == 2) run_class(Int<2>{}, n);
+        else if constexpr (NS > 3) {
+          if (phase == 3) run_class(Int<3>{}, n);
+          else if constexpr (NS > 4) {
+            if (phase == 4) run_class(Int<4>{}, n);
+            else if constexpr (NS > 5) {
+              if (phase == 5) run_class(Int<5>{}, n);
+              else if constexpr (NS > 6) {
+                if (phase == 6) run_class(Int<6>{}, n);
+                else if constexpr (NS > 7) run_class(Int<7>{}, n);
+              }
+            }
+          }
+        }
+      }
+      if constexpr (!AL) phase = (phase + n) % NS;
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) tot[i][j] = tot[i][j] + acc[i][j];
+    }
+    if constexpr (SL) {
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < CB; ++j) sum[i][j] = sl == 0 ? tot[i][j] : sum[i][j] + tot[i][j];
+    }
+  }
+  wait_vm<0>();  // no load may land after the workgroup's LDS is released
+
+  wg_barrier();  // every wave is past its last read of a stage
+  float* tw = reinterpret_cast<float*>(s0) + wave * 256;
+  float* part = KIND == EPI_PARTIAL ? e.part + (int64_t)split * sh.M * sh.N : nullptr;
+#pragma unroll
+  for (int i = 0; i < MT; ++i) {
+    const int mb = mb0 + wm * MT + i;
+    if (16 * mb >= sh.M) break;  // wave-uniform
+    // the rotary entries of a row tile's blocks are requested together
+    f32x4 cs[KIND == EPI_QKV ? CB : 1], sn[KIND == EPI_QKV ? CB : 1];
+    if constexpr (KIND == EPI_QKV) {
+      const int hd = e.hd, bh = hd / 16;
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        const int blk = sh.nb_off + min(cb0 + wn * CB + j, nbc - 1);
+        cs[j] = f32x4{1.f, 1.f, 1.f, 1.f};
+        sn[j] = zero;
+        if (blk < 2 * e.H * bh) {  // wave-uniform
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {  // rows past M read position 0
+            const int64_t ti = (int64_t)rm[16 * (wm * MT + i) + 4 * (lane >> 4) + r].pos * (hd / 2) + 8 * (blk % bh) + (lane & 7);
+            cs[j][r] = e.rcos[ti];
+            sn[j][r] = e.rsin[ti];
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < CB; ++j) {
+      const int cj = cb0 + wn * CB + j;
+      if (cj >= nbc) break;  // wave-uniform
+      f32x4 v;
+      if constexpr (SL) v = sum[i][j];
+      else v = tot[i][j];
+      constexpr int jq = KIND == EPI_QKV ? 1 : 0;
+      store_tile<T, KIND>(sh, e, mb, sh.nb_off + cj, v, part, tw, jq ? rm + 16 * (wm * MT + i) : rm, cs[jq ? j : 0],
+                          sn[jq ? j : 0], lane);
+    }
+  }
+}
+
+}  // namespace
+
+namespace {
+
+// Output tiles: rows x 16-column blocks per workgroup, and the time of one
+// round of a launch with them on 256 CUs (us, K = 4096).
+enum Tile { BIG, MED, SQ, SML };
+constexpr int TILE_ROWS[] = {256, 256, 128, 128};
+constexpr int TILE_BLKS[] = {8, 6, 8, 6};
+
+int tiles_of(Tile t, int M, int nbc) {
+  return (M + TILE_ROWS[t] - 1) / TILE_ROWS[t] * ((nbc + TILE_BLKS[t] - 1) / TILE_BLKS[t]);
+}
+
+// Unsplit launches: the tile with the fewest rounds, weighted by the measured
+// time of a round.  256-row tiles run one workgroup per CU (64 us a round with
+// 128 columns, 57 us with 96), 128-row tiles two (74 and 65 us, or 46 and
+// 43 us when the launch has at most one per CU).
+Tile pick_tile(int M, int nbc) {
+  auto cost = [&](Tile t) {
+    const int n = tiles_of(t, M, nbc);
+    switch (t) {
+      case BIG: return (n + 255) / 256 * 64;
+      case MED: return (n + 255) / 256 * 57;
+      case SQ: return n <= 256 ? 46 : (n + 511) / 512 * 74;
+      default: return n <= 256 ? 43 : (n + 511) / 512 * 65;
+    }
+  };
+  Tile best = BIG;
+  for (Tile t : {MED, SQ, SML})
+    if (cost(t) < cost(best)) best = t;
+  return best;
+}
+
+// Split-K shapes.  With at least 192 256x128 tiles a launch fills the chip by
+// itself: each workgroup runs its slices one after another and adds them in
+// registers (at 2048 x 4096 x 4096 65 us against 91 us with the slices side
+// by side, and the consumer reads one partial instead of four).  Smaller ones
+// put the slices side by side, on 256-row tiles if that makes 256 workgroups.
+constexpr int SLICES_IN_WG_TILES = 192;
+bool slices_in_wg(int M, int nbc) { return tiles_of(BIG, M, nbc) >= SLICES_IN_WG_TILES; }
+
+template <typename T, int KIND, int WM, int WN, int MT, int CB, bool SL>
+void go(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
+  constexpr int NS = 4;
+  const int nbc = s.nb_count ? s.nb_count : s.N / 16;
+  const int nrb = (s.M + 16 * WM * MT - 1) / (16 * WM * MT), ncb = (nbc + WN * CB - 1) / (WN * CB);
+  const int kps = s.K / (4 * ET<T>::VEC) / s.splits;
+  const dim3 grid(nrb * ncb * (SL ? 1 : s.splits)), wg(64 * WM * WN);
+  const bool al = kps % (4 * NS) == 0;
+  if (ea || eb) {
+    if (al)
+      hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, true>), grid, wg, 0, st, ea, eb, 0, s, e,
+                            nrb, ncb);
+    else
+      hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, false>), grid, wg, 0, st, ea, eb, 0, s,
+                            e, nrb, ncb);
+    return;
+  }
+  if (al)
+    hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, true>), grid, wg, 0, st, s, e, nrb, ncb);
+  else
+    hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, false>), grid, wg, 0, st, s, e, nrb, ncb);
+}
+
+template <int KIND>
+void go_unsplit(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
+  switch (pick_tile(s.M, s.nb_count ? s.nb_count : s.N / 16)) {
+    case BIG: go<bf16_t, KIND, 4, 2, 4, 4, false>(s, e, st, ea, eb); break;
+    case MED: go<bf16_t, KIND, 4, 2, 4, 3, false>(s, e, st, ea, eb); break;
+    case SQ: go<bf16_t, KIND, 4, 2, 2, 4, false>(s, e, st, ea, eb); break;
+    default: go<bf16_t, KIND, 4, 2, 2, 3, false>(s, e, st, ea, eb); break;
+  }
+}
+
+template <int KIND>
+void go_slices(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
+  go<bf16_t, KIND, 4, 2, 4, 4, true>(s, e, st, ea, eb);
+}
+
+}  // namespace
+
+bool gemm_wide_takes(int dtype, int M, int K, int x_mtiles) {
+  // up to 128 rows the row-split-free kernel is faster (QKV at 128 rows 33 us
+  // against 37 us); its K offsets are 32-bit
+  return dtype == DT_BF16 && M > 128 && (int64_t)K * 16 * x_mtiles * 2 < (int64_t)1 << 32 && K < 1 << 24;
+}
+
+bool gemm_wide_sums_slices(int M, int nbc, int kind) {
+  return (kind == EPI_PARTIAL || kind == EPI_F32 || kind == EPI_SILU) && slices_in_wg(M, nbc);
+}
+
+void launch_gemm_wide(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
+  const int nbc = s.nb_count ? s.nb_count : s.N / 16;
+  if (s.splits > 1 && gemm_wide_sums_slices(s.M, nbc, e.kind)) {
+    if (e.kind == EPI_PARTIAL) go_slices<EPI_PARTIAL>(s, e, st, ea, eb);
+    else if (e.kind == EPI_F32) go_slices<EPI_F32>(s, e, st, ea, eb);
+    else go_slices<EPI_SILU>(s, e, st, ea, eb);
+  } else if (e.kind == EPI_PARTIAL) {
+    if (tiles_of(BIG, s.M, nbc) * s.splits >= 256)
+      go<bf16_t, EPI_PARTIAL, 4, 2, 4, 4, false>(s, e, st, ea, eb);
+    else
+      go<bf16_t, EPI_PARTIAL, 4, 2, 2, 4, false>(s, e, st, ea, eb);
+  } else if (e.kind == EPI_F32) {
+    go_unsplit<EPI_F32>(s, e, st, ea, eb);
+  } else if (e.kind == EPI_SILU) {
+    go_unsplit<EPI_SILU>(s, e, st, ea, eb);
+  } else if (e.kind == EPI_SWIGLU) {
+    go_unsplit<EPI_SWIGLU>(s, e, st, ea, eb);
+  } else {
+    go_unsplit<EPI_QKV>(s, e, st, ea, eb);
+  }
+}

@@ -706,11 +706,12 @@ __device__ __forceinline__ void trigram_row(const StepState& s, const T* E, int 
   int tk[3];
 #pragma unroll
   for (int part = 0; part < 3; ++part) tk[part] = pos - 2 + part >= 0 ? path_token(s, b, node, pos - 2 + part) : -1;
-  for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < 3 * d; i += gridDim.y * blockDim.x) {
+  constexpr int VEC = ET<T>::VEC;  // 16-byte pieces; d is a multiple of 256
+  for (int i = VEC * (blockIdx.y * blockDim.x + threadIdx.x); i < 3 * d; i += VEC * gridDim.y * blockDim.x) {
     const int part = i / d, col = i % d;
-    T v = ET<T>::from_f(0.f);
-    if (tk[part] >= 0) v = E[(int64_t)tk[part] * d + col];
-    copy_tiled<T>(dst, mtiles, row, i, v);
+    int4 v = int4{0, 0, 0, 0};
+    if (tk[part] >= 0) v = ld16(E + (int64_t)tk[part] * d + col);
+    st16(dst + tiled_index<T>(mtiles, row, i), v);
   }
 }
 
@@ -758,8 +759,9 @@ __global__ void draft_rows_kernel(StepState s, const T* E, DraftLevel lv, T* tri
   if (want_tri && valid) {
     trigram_row<T>(s, E, b, node, p, tri_in, tri_mtiles, r);
   } else {
-    for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < 3 * s.d; i += gridDim.y * blockDim.x)
-      copy_tiled<T>(tri_in, tri_mtiles, r, i, ET<T>::from_f(0.f));
+    constexpr int VEC = ET<T>::VEC;
+    for (int i = VEC * (blockIdx.y * blockDim.x + threadIdx.x); i < 3 * s.d; i += VEC * gridDim.y * blockDim.x)
+      st16(tri_in + tiled_index<T>(tri_mtiles, r, i), int4{0, 0, 0, 0});
   }
 }
 
@@ -782,26 +784,42 @@ __global__ __launch_bounds__(256) void draft_finish_kernel(StepState s, DraftLev
   }
 }
 
+// Row i of a prefill chunk: its segment, position and descriptors, and (with
+// a draft) its trigram input and the encoder descriptors of its two entries.
+// Workgroup 0 also writes the chunk's attention blocks.
 template <typename T>
-__global__ void prefill_rows_kernel(StepState s, const T* E, int b, int p0, int M, int* tokens_out, T* tri_in,
-                                    int tri_mtiles, int* enc_pos, int64_t* enc_kvoff, int* enc_qrow, int* pf_n) {
-  const int i = blockIdx.x;
-  const int p = p0 + i;
+__global__ __launch_bounds__(256) void prefill_rows_kernel(StepState s, const T* E, PrefillChunk c, int* tokens_out,
+                                                           PrefillBlock* blk, int draft, T* tri_in, int tri_mtiles,
+                                                           int* enc_pos, int64_t* enc_kvoff, int* enc_qrow) {
+  const int i = blockIdx.x, M = c.row0[c.n_seg];
+  int k = 0;
+  while (i >= c.row0[k + 1]) ++k;
+  const int b = c.seq[k], p = c.p0[k] + i - c.row0[k];
   if (threadIdx.x == 0) {
     const int* ptab = s.page_table + (int64_t)b * s.max_pages;
     s.v_pos[i] = p;
     s.v_qrow[i] = i;
     s.v_kvoff[i] = (int64_t)ptab[p / s.ps] * s.page_stride + (int64_t)(p % s.ps) * s.hd;
     tokens_out[i] = s.tok[(int64_t)b * s.tok_stride + p];
-    enc_pos[i] = p;
-    enc_kvoff[i] = enc_off(s, b, 0, p);
-    enc_qrow[i] = -1;
-    enc_pos[M + i] = p;
-    enc_kvoff[M + i] = enc_off(s, b, 1, p);
-    enc_qrow[M + i] = -1;
-    if (i == 0) pf_n[0] = p0;  // committed length seen by the chunk's attention
+    if (draft) {
+      enc_pos[i] = p;
+      enc_kvoff[i] = enc_off(s, b, 0, p);
+      enc_qrow[i] = -1;
+      enc_pos[M + i] = p;
+      enc_kvoff[M + i] = enc_off(s, b, 1, p);
+      enc_qrow[M + i] = -1;
+    }
   }
-  trigram_row<T>(s, E, b, -1, p, tri_in, tri_mtiles, i);
+  if (i == 0) {
+    int first = 0;  // blocks of the segments before
+    for (int q = 0; q < c.n_seg; ++q) {
+      const int rows = c.row0[q + 1] - c.row0[q], nb = (rows + 63) / 64;
+      for (int t = threadIdx.x; t < nb; t += blockDim.x)
+        blk[first + t] = PrefillBlock{c.row0[q] + 64 * t, c.p0[q] + 64 * t, min(64, rows - 64 * t), c.seq[q]};
+      first += nb;
+    }
+  }
+  if (draft) trigram_row<T>(s, E, b, -1, p, tri_in, tri_mtiles, i);
 }
 
 // ---------------------------------------------------------------------------
@@ -899,10 +917,12 @@ __global__ __launch_bounds__(256) void tri_insert_kernel(StepState s, TriCache c
   if (!row_of(r, b, node, p)) return;
   const unsigned long long key = tri_key(s, b, node, p);
   const int set = tri_set(key, c.n_sets);
-  for (int r2 = 0; r2 < r; ++r2) {  // an earlier row of this launch owns the set
+  bool taken = false;  // an earlier row of this launch owns the set
+  for (int r2 = threadIdx.x; r2 < r && !taken; r2 += 256) {
     int b2, n2, p2;
-    if (row_of(r2, b2, n2, p2) && tri_set(tri_key(s, b2, n2, p2), c.n_sets) == set) return;
+    taken = row_of(r2, b2, n2, p2) && tri_set(tri_key(s, b2, n2, p2), c.n_sets) == set;
   }
+  if (__syncthreads_or(taken)) return;
   if (threadIdx.x == 0) {
     int v = 0, hitw = -1;
     unsigned int best = 0xffffffffu;
@@ -929,16 +949,30 @@ __global__ __launch_bounds__(256) void tri_insert_kernel(StepState s, TriCache c
   }
 }
 
+// Prompts that end in a chunk: workgroup j copies the last row's state of
+// prompt j to h_last and to row j of the LM head's input.
 template <typename T>
-__global__ void prefill_finish_kernel(StepState s, int b, int n, const int* amax_row, const T* hl_row) {
-  const int d = s.d;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) ((T*)s.h_last)[(int64_t)b * d + i] = hl_row[i];
-  if (threadIdx.x == 0) {
-    s.tok[(int64_t)b * s.tok_stride + n] = amax_row[0];
-    s.n[b] = n;
-    s.pro_base[b] = n;
-    s.pro_count[b] = 0;
+__global__ __launch_bounds__(256) void prefill_last_kernel(StepState s, PrefillEnds e, const T* hl_rm, T* out,
+                                                           int o_mtiles) {
+  const int j = blockIdx.x, d = s.d;
+  constexpr int VEC = ET<T>::VEC;
+  const T* src = hl_rm + (int64_t)e.row[j] * d;
+  T* hl = (T*)s.h_last + (int64_t)e.seq[j] * d;
+  for (int i = VEC * threadIdx.x; i < d; i += VEC * 256) {
+    const int4 v = ld16(src + i);
+    st16(hl + i, v);
+    st16(out + tiled_index<T>(o_mtiles, j, i), v);
   }
+}
+
+__global__ void prefill_finish_kernel(StepState s, PrefillEnds e, const int* first) {
+  const int j = threadIdx.x;
+  if (j >= e.n) return;
+  const int b = e.seq[j], n = e.len[j];
+  s.tok[(int64_t)b * s.tok_stride + n] = first[j];
+  s.n[b] = n;
+  s.pro_base[b] = n;
+  s.pro_count[b] = 0;
 }
 
 }  // namespace
@@ -1048,7 +1082,8 @@ int draft_level_rows(const StepState& s, const DraftLevel& lv) {
 
 void launch_draft_rows(int dtype, const StepState& s, const void* E, const DraftLevel& lv, void* tri_in,
                        int tri_mtiles, int* pos, int64_t* kvoff, int* qrow, hipStream_t st) {
-  const dim3 grid(draft_level_rows(s, lv), (3 * s.d + 255) / 256);
+  const int pieces = 3 * s.d / (dtype == DT_BF16 ? 8 : 4);
+  const dim3 grid(draft_level_rows(s, lv), (pieces + 255) / 256);
   if (dtype == DT_BF16)
     hipLaunchKernelGGL(draft_rows_kernel<bf16_t>, grid, dim3(256), 0, st, s, (const bf16_t*)E, lv,
                        (bf16_t*)tri_in, tri_mtiles, pos, kvoff, qrow);
@@ -1068,15 +1103,16 @@ void launch_draft_finish(int dtype, const StepState& s, const DraftLevel& lv, co
                        (float*)zin, z_mtiles);
 }
 
-void launch_prefill_rows(int dtype, const StepState& s, const void* E, int b, int p0, int M, int* tokens_out,
-                         void* tri_in, int tri_mtiles, int* enc_pos, int64_t* enc_kvoff, int* enc_qrow, int* pf_n,
-                         hipStream_t st) {
+void launch_prefill_rows(int dtype, const StepState& s, const void* E, const PrefillChunk& c, int* tokens_out,
+                         PrefillBlock* blk, int draft, void* tri_in, int tri_mtiles, int* enc_pos, int64_t* enc_kvoff,
+                         int* enc_qrow, hipStream_t st) {
+  const dim3 grid(c.row0[c.n_seg]);
   if (dtype == DT_BF16)
-    hipLaunchKernelGGL(prefill_rows_kernel<bf16_t>, dim3(M), dim3(256), 0, st, s, (const bf16_t*)E, b, p0, M,
-                       tokens_out, (bf16_t*)tri_in, tri_mtiles, enc_pos, enc_kvoff, enc_qrow, pf_n);
+    hipLaunchKernelGGL(prefill_rows_kernel<bf16_t>, grid, dim3(256), 0, st, s, (const bf16_t*)E, c, tokens_out, blk,
+                       draft, (bf16_t*)tri_in, tri_mtiles, enc_pos, enc_kvoff, enc_qrow);
   else
-    hipLaunchKernelGGL(prefill_rows_kernel<float>, dim3(M), dim3(256), 0, st, s, (const float*)E, b, p0, M, tokens_out,
-                       (float*)tri_in, tri_mtiles, enc_pos, enc_kvoff, enc_qrow, pf_n);
+    hipLaunchKernelGGL(prefill_rows_kernel<float>, grid, dim3(256), 0, st, s, (const float*)E, c, tokens_out, blk, draft,
+                       (float*)tri_in, tri_mtiles, enc_pos, enc_kvoff, enc_qrow);
 }
 
 void launch_tri_lookup(const StepState& s, const TriCache& c, const DraftLevel& lv, float* htri, hipStream_t st) {
@@ -1089,14 +1125,18 @@ void launch_tri_insert(const StepState& s, const TriCache& c, const DraftLevel& 
   hipLaunchKernelGGL(tri_insert_kernel, dim3(rows), dim3(256), 0, st, s, c, lv, b, p0, prefill_M, vals);
 }
 
-void launch_prefill_finish(int dtype, const StepState& s, int b, int n, const int* amax_row, const void* hl_row,
-                           hipStream_t st) {
+void launch_prefill_last(int dtype, const StepState& s, const PrefillEnds& e, const void* hl_rm, void* out,
+                         int o_mtiles, hipStream_t st) {
   if (dtype == DT_BF16)
-    hipLaunchKernelGGL(prefill_finish_kernel<bf16_t>, dim3(1), dim3(256), 0, st, s, b, n, amax_row,
-                       (const bf16_t*)hl_row);
+    hipLaunchKernelGGL(prefill_last_kernel<bf16_t>, dim3(e.n), dim3(256), 0, st, s, e, (const bf16_t*)hl_rm,
+                       (bf16_t*)out, o_mtiles);
   else
-    hipLaunchKernelGGL(prefill_finish_kernel<float>, dim3(1), dim3(256), 0, st, s, b, n, amax_row,
-                       (const float*)hl_row);
+    hipLaunchKernelGGL(prefill_last_kernel<float>, dim3(e.n), dim3(256), 0, st, s, e, (const float*)hl_rm, (float*)out,
+                       o_mtiles);
+}
+
+void launch_prefill_finish(const StepState& s, const PrefillEnds& e, const int* first, hipStream_t st) {
+  hipLaunchKernelGGL(prefill_finish_kernel, dim3(1), dim3(64), 0, st, s, e, first);
 }
 
 // ---- phase timestamps ---------------------------------------------------------

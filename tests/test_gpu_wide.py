@@ -1,0 +1,75 @@
+"""Launches of many rows: the 2-D tiled GEMM and the packed prefill chunks.
+
+A row's arithmetic does not depend on how many rows a launch carries, so every
+comparison here is exact: a product of 129 to 256 rows (the tiled kernel)
+against the same rows in launches of at most 128 (the streaming kernel), and
+prompts prefilled together, in chunks of up to 2048 rows, against each prompt
+prefilled alone."""
+import numpy as np
+import pytest
+import torch  # before the library: both then share one HIP runtime
+
+import synth
+from paper_2402_15758_amd import Session
+from paper_2402_15758_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+
+def _gemm(dtype, x, w):
+    (M, K), N = x.shape, w.shape[1]
+    y = np.zeros((M, N), dtype=np.float32)
+    B.chimera_debug_gemm(dtype, x.ctypes.data, w.ctypes.data, M, N, K, y.ctypes.data)
+    return y
+
+
+# N, K: one 16-column group up to unsplit width; K below one k-block per wave,
+# ragged classes (K / 32 not a multiple of 16), split K with even and odd slices
+@pytest.mark.parametrize("N,K", [(64, 32), (64, 96), (192, 544), (320, 1024), (2048, 2048), (1088, 5504), (8256, 160)])
+def test_rows_keep_their_bits_in_wide_launches(N, K):
+    print(f"wide gemm N={N} K={K}", flush=True)
+    torch.cuda.init()
+    rng = np.random.default_rng(N + K)
+    x = (rng.standard_normal((256, K)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    w = (rng.standard_normal((K, N)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    ref = np.concatenate([_gemm(B.CHIMERA_BF16, x[:128].copy(), w), _gemm(B.CHIMERA_BF16, x[128:].copy(), w)])
+    for M in (129, 200, 256):
+        y = _gemm(B.CHIMERA_BF16, x[:M].copy(), w)
+        assert np.array_equal(y.view(np.uint32), ref[:M].view(np.uint32)), f"M={M}"
+
+
+def _states(sess):
+    """What two steps after the prefill show of every sequence."""
+    out = [[] for _ in range(sess.batch)]
+    for _ in range(2):
+        toks, n, path = sess.step()
+        logits = sess.debug(B.DBG_VERIFY_LOGITS).reshape(sess.batch, sess.n_nodes, -1).view(np.uint32)
+        tree = sess.debug(B.DBG_TREE_TOKENS)
+        for b, o in enumerate(out):
+            o += [toks[b], n[b], path[b], logits[b], tree[b]]
+    return out
+
+
+@pytest.mark.parametrize("model,lens", [
+    ("tiny", (1, 64, 65)),
+    ("tiny", (200, 17, 130)),
+    ("small", (63, 129, 640)),
+    ("small", (1500, 2, 900)),   # the third prompt is cut at a chunk's end
+    ("small", (2049,)),          # one row past the largest chunk
+])
+def test_prompts_prefilled_together_equal_each_alone(model, lens):
+    print(f"packed prefill: {model}, prompts {lens}", flush=True)
+    cfg = synth.TINY if model == "tiny" else synth.small_config()
+    w = synth.make_weights(cfg, device="cuda", std=0.06)
+    prompts = [synth.make_prompt(n, cfg.vocab, 40 + i) for i, n in enumerate(lens)]
+    max_len = max(lens) + 128
+    every = Session(cfg, w, synth.TREE_T8, max_batch=len(lens), max_len=max_len)
+    first = every.prefill(prompts)
+    together = _states(every)
+    for b, p in enumerate(prompts):
+        one = Session(cfg, None, synth.TREE_T8, max_batch=1, max_len=max_len, share_model=every)
+        assert int(one.prefill([p])[0]) == int(first[b])
+        for got, want in zip(together[b], _states(one)[0]):
+            assert np.array_equal(got, want)
+        one.close()
+    every.close()
