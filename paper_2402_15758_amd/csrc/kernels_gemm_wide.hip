@@ -7,19 +7,24 @@
 // The streaming kernel gives each of its four waves one class, so a workgroup
 // re-reads its activation rows for every run of 6 columns blocks: fine while
 // the weight stream is what is waited for, and 430-600 TFLOP/s on 2048 rows.
-// Here a workgroup owns a tile of up to 256 rows x 128 columns, its eight
+// Here a workgroup owns a tile of up to 256 rows x 192 columns, its eight
 // waves 64 x 64 (two a SIMD: 64 accumulators, 64 totals and, with the slices
-// added in registers, 64 sums fit their 256 registers), and the classes run
+// added in registers, 64 sums fit their 256 registers) or 64 x 96, and the classes run
 // one after another.  Operand tiles go from memory straight into a ring of
 // four LDS stages (global_load_lds, 1 KiB a wave: fragment order is what such
 // a load writes), so a stage costs no registers and one barrier.
 //
-// What bounds it: LDS.  A k-block of the 256 x 128 tile is 512 cycles of MFMA
-// on every SIMD and 88 KiB through LDS (64 read, 24 written).  Measured
-// against the streaming kernel, 7B shapes, us: 2048 rows QKV 477 -> 230, O
-// 153 -> 68, gate/up 620 -> 365, down 319 -> 167 (1.1 PFLOP/s); 256 rows QKV
-// 46 -> 43, O 22 -> 16, gate/up 76 -> 61, down 43 -> 34, LM head 119 -> 75.
-// More stages (6, 8) and fragments read a step ahead were no faster.
+// What bounds it: the operand tiles on their way into LDS.  The loads alone
+// take 296 of the 388 us of a 2048-row gate/up on 256x128 tiles, the MFMAs
+// alone 227 us (1.6 PFLOP/s, this card's matrix rate) and the LDS reads 120
+// us; each CU takes in 50-60 GB/s whatever the ring's depth (3 to 8 stages
+// measured) or the order of the tiles over the dies.  So the tile is as large
+// as the registers allow, 256x192 (28 KiB a k-block for 1.5 times the work of
+// 24 KiB): gate/up at 512 rows 107 -> 86 us, 1024 rows 187 -> 170 us, QKV at
+// 1024 rows 117 -> 94 us.  Against the streaming kernel, 7B shapes, us: 2048
+// rows QKV 477 -> 230, O 153 -> 68, gate/up 620 -> 365, down 319 -> 167; 256
+// rows QKV 46 -> 43, O 22 -> 16, gate/up 76 -> 61, down 43 -> 34, LM head 119
+// -> 75.  Fragments read a step ahead of their MFMAs were no faster.
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -361,30 +366,33 @@ namespace {
 
 // Output tiles: rows x 16-column blocks per workgroup, and the time of one
 // round of a launch with them on 256 CUs (us, K = 4096).
-enum Tile { BIG, MED, SQ, SML };
-constexpr int TILE_ROWS[] = {256, 256, 128, 128};
-constexpr int TILE_BLKS[] = {8, 6, 8, 6};
+enum Tile { XL, BIG, MED, SQ, SML };
+constexpr int TILE_ROWS[] = {256, 256, 256, 128, 128};
+constexpr int TILE_BLKS[] = {12, 8, 6, 8, 6};
 
 int tiles_of(Tile t, int M, int nbc) {
   return (M + TILE_ROWS[t] - 1) / TILE_ROWS[t] * ((nbc + TILE_BLKS[t] - 1) / TILE_BLKS[t]);
 }
 
 // Unsplit launches: the tile with the fewest rounds, weighted by the measured
-// time of a round.  256-row tiles run one workgroup per CU (64 us a round with
-// 128 columns, 57 us with 96), 128-row tiles two (74 and 65 us, or 46 and
-// 43 us when the launch has at most one per CU).
-Tile pick_tile(int M, int nbc) {
+// time of a round.  256-row tiles run one workgroup per CU (90 us a round with
+// 192 columns, 64 with 128, 57 with 96), 128-row tiles two (74 and 65 us, or
+// 46 and 43 us when the launch has at most one per CU).  The 192-column tile
+// exists for reductions of whole rounds of the ring only (K a multiple of 512:
+// the general one would spill).
+Tile pick_tile(int M, int nbc, int kps) {
   auto cost = [&](Tile t) {
     const int n = tiles_of(t, M, nbc);
     switch (t) {
+      case XL: return kps % 16 == 0 ? (n + 255) / 256 * 90 : 1 << 30;
       case BIG: return (n + 255) / 256 * 64;
       case MED: return (n + 255) / 256 * 57;
       case SQ: return n <= 256 ? 46 : (n + 511) / 512 * 74;
       default: return n <= 256 ? 43 : (n + 511) / 512 * 65;
     }
   };
-  Tile best = BIG;
-  for (Tile t : {MED, SQ, SML})
+  Tile best = XL;
+  for (Tile t : {BIG, MED, SQ, SML})
     if (cost(t) < cost(best)) best = t;
   return best;
 }
@@ -409,20 +417,21 @@ void go(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hip
     if (al)
       hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, true>), grid, wg, 0, st, ea, eb, 0, s, e,
                             nrb, ncb);
-    else
+    else if constexpr (CB < 6)
       hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, false>), grid, wg, 0, st, ea, eb, 0, s,
                             e, nrb, ncb);
     return;
   }
   if (al)
     hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, true>), grid, wg, 0, st, s, e, nrb, ncb);
-  else
+  else if constexpr (CB < 6)
     hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, false>), grid, wg, 0, st, s, e, nrb, ncb);
 }
 
 template <int KIND>
 void go_unsplit(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
-  switch (pick_tile(s.M, s.nb_count ? s.nb_count : s.N / 16)) {
+  switch (pick_tile(s.M, s.nb_count ? s.nb_count : s.N / 16, s.K / (4 * ET<bf16_t>::VEC) / s.splits)) {
+    case XL: go<bf16_t, KIND, 4, 2, 4, 6, false>(s, e, st, ea, eb); break;
     case BIG: go<bf16_t, KIND, 4, 2, 4, 4, false>(s, e, st, ea, eb); break;
     case MED: go<bf16_t, KIND, 4, 2, 4, 3, false>(s, e, st, ea, eb); break;
     case SQ: go<bf16_t, KIND, 4, 2, 2, 4, false>(s, e, st, ea, eb); break;

@@ -24,8 +24,10 @@ def _gemm(dtype, x, w):
 
 
 # N, K: one 16-column group up to unsplit width; K below one k-block per wave,
-# ragged classes (K / 32 not a multiple of 16), split K with even and odd slices
-@pytest.mark.parametrize("N,K", [(64, 32), (64, 96), (192, 544), (320, 1024), (2048, 2048), (1088, 5504), (8256, 160)])
+# ragged classes (K / 32 not a multiple of 16), split K with even and odd slices;
+# 33024 columns: the widest tile
+@pytest.mark.parametrize("N,K", [(64, 32), (64, 96), (192, 544), (320, 1024), (2048, 2048), (1088, 5504), (8256, 160),
+                                 (33024, 512)])
 def test_rows_keep_their_bits_in_wide_launches(N, K):
     print(f"wide gemm N={N} K={K}", flush=True)
     torch.cuda.init()
