@@ -204,9 +204,9 @@ chimera_status chimera_profile_read(chimera_ctx* ctx, chimera_profile* out);
 
 /* Launch mode of chimera_step: 1 (default) captures the step's launch
  * sequence once into a HIP graph and replays it every step (recaptured after
- * prefill, set_forcing, set_drafting, set_decoding, set_trigram_cache or a
- * stream change; needs a non-null stream); 0 launches every kernel
- * individually.  Results are identical. */
+ * a prefill of another batch size, set_forcing, set_drafting, set_decoding,
+ * set_trigram_cache or a stream change; needs a non-null stream); 0 launches
+ * every kernel individually.  Results are identical. */
 chimera_status chimera_set_graph(chimera_ctx* ctx, int32_t enable);
 
 /* Verification rule (Sec. 4.3; Sec. 5.1 tests greedy and typical decoding at

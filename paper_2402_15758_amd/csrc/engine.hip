@@ -261,6 +261,7 @@ struct chimera_ctx {
   hipGraphExec_t gexec = nullptr;
   bool capturing = false;  // chimera_step is capturing its launch sequence
   hipStream_t graph_stream = nullptr;
+  int graph_batch = 0;  // the only thing a prefill changes that the captured launches depend on
   size_t graph_ev_used = 0;
 };
 
@@ -1221,7 +1222,6 @@ chimera_status chimera_prefill(chimera_model* m, chimera_kv* kv, chimera_ctx* ct
     }
     hipStream_t st = (hipStream_t)stream;
     ctx->batch = batch;
-    drop_graph(ctx);
     StepState s = make_state(ctx);
     off = 0;
     for (int b = 0; b < batch; ++b) {
@@ -1328,7 +1328,7 @@ void enqueue_step(chimera_ctx* ctx, hipStream_t st) {
     mark(3, q);
   };
   if (use_graph) {
-    if (ctx->gexec == nullptr || ctx->graph_stream != st) {
+    if (ctx->gexec == nullptr || ctx->graph_stream != st || ctx->graph_batch != ctx->batch) {
       drop_graph(ctx);
       HIPCK(hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
       ctx->capturing = true;
@@ -1345,6 +1345,7 @@ void enqueue_step(chimera_ctx* ctx, hipStream_t st) {
       HIPCK(hipStreamEndCapture(st, &ctx->graph));
       HIPCK(hipGraphInstantiate(&ctx->gexec, ctx->graph, nullptr, nullptr, 0));
       ctx->graph_stream = st;
+      ctx->graph_batch = ctx->batch;
       ctx->graph_ev_used = ctx->ev_used;
     }
     ctx->ev_used = ctx->graph_ev_used;

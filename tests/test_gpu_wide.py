@@ -75,3 +75,22 @@ def test_prompts_prefilled_together_equal_each_alone(model, lens):
             assert np.array_equal(got, want)
         one.close()
     every.close()
+
+
+def test_step_graph_survives_a_prefill_of_the_same_batch():
+    """Requests one after another on one session, batch 2, 2, 1, 2: every
+    step equals that of a session launching its kernels one by one."""
+    print("graph across prefills", flush=True)
+    cfg = synth.small_config()
+    w = synth.make_weights(cfg, device="cuda", std=0.06)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        graph = Session(cfg, w, synth.TREE_T32, max_batch=2, max_len=256)
+        eager = Session(cfg, None, synth.TREE_T32, max_batch=2, max_len=256, share_model=graph)
+        eager.set_graph(False)
+        for r, lens in enumerate([(40, 77), (77, 9), (50,), (33, 64)]):
+            prompts = [synth.make_prompt(n, cfg.vocab, 10 * r + i) for i, n in enumerate(lens)]
+            assert np.array_equal(graph.prefill(prompts), eager.prefill(prompts))
+            for got, want in zip(_states(graph), _states(eager)):
+                assert all(np.array_equal(a, b) for a, b in zip(got, want))
+        graph.close()
+        eager.close()
