@@ -14,7 +14,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libchimera.so")
-SOURCES = ["kernels_gemm_wide.hip", "kernels_gemm.hip", "kernels_attn.hip", "kernels_misc.hip", "engine.hip"]
+SOURCES = ["kernels_gemm_wide.hip", "kernels_gemm.hip", "kernels_gemm_rows.hip", "kernels_attn.hip", "kernels_misc.hip", "engine.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

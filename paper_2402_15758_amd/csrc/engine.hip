@@ -517,7 +517,7 @@ void run_draft(chimera_ctx* c, const StepState& s, hipStream_t st) {
     const DraftLevel lv{k, c->lvl_R[k], c->lvl_off[k]};
     const int Q = B * lv.R;              // query rows
     const int Mk = draft_level_rows(s, lv);  // plus the prologue rows at level 0
-    launch_draft_rows(dt, s, m->embed, lv, c->tri_in, c->mt_d, c->d_pos, c->d_kvoff, c->d_qrow, st);
+    launch_draft_rows(dt, s, m->embed, lv, c->tri_in, c->mt_d, c->d_pos, c->d_kvoff, c->d_qrow, c->zin, c->mt_q, st);
     // trigram encoder (Eq. 2); with the cache, hits fill their rows and the MLP
     // launches do nothing when every row hit
     const int* tri_skip = nullptr;
@@ -587,11 +587,18 @@ void run_draft(chimera_ctx* c, const StepState& s, hipStream_t st) {
     egu.out_t = c->hc;
     egu.o_mtiles = c->mt_q;
     g.run(c->yn, c->mt_q, Q, m->enc.wgu, 2 * F, d, egu);
+    // zin = [h_last; x + FFN]: the draft rows have put h_last in place, the
+    // down projection adds the residual itself where it sums its own slices
     GemmEpi ed;
-    ed.kind = EPI_PARTIAL;
+    ed.out_t = c->zin;
+    ed.o_mtiles = c->mt_q;
+    ed.out_f = c->htri;
+    ed.ldo = d;
     ed.part = c->dparts;
+    ed.kind = gemm_rows_takes(dt, Q, F, gemm_pick_splits(d, F, dt), EPI_ZIN) ? EPI_ZIN : EPI_PARTIAL;
     g.run(c->hc, c->mt_q, Q, m->enc.wdown, d, F, ed);
-    launch_draft_finish(dt, s, lv, c->htri, c->dparts, gemm_partials(dt, Q, d, F, c->mt_q), c->zin, c->mt_q, st);
+    if (ed.kind == EPI_PARTIAL)
+      launch_draft_finish(dt, s, lv, c->htri, c->dparts, gemm_partials(dt, Q, d, F, c->mt_q), c->zin, c->mt_q, st);
     GemmEpi ea1;
     ea1.kind = EPI_SILU;
     ea1.out_t = c->ak;

@@ -113,4 +113,74 @@ __device__ __forceinline__ void qkv_store16(const GemmEpi& e, const RowMeta& rm,
   }
 }
 
+// Store one 16x16 output tile (row block mb, column block blk): v in MFMA
+// layout (lane (g, c16): rows 4g .. 4g+3, column c16).  tw: 1 KiB of LDS of
+// this wave.  rm: row targets of the tile's 16 rows (QKV).
+template <typename T, int KIND>
+__device__ __forceinline__ void store_tile(const GemmShape& sh, const GemmEpi& e, int mb, int blk, f32x4 v, float* part,
+                                           float* tw, const RowMeta* rm, f32x4 cs, f32x4 sn, int lane) {
+  const int g = lane >> 4, c16 = lane & 15;
+  if constexpr (KIND == EPI_F32 || KIND == EPI_PARTIAL) {
+    float* base = KIND == EPI_F32 ? e.out_f : part;
+    const int64_t ld = KIND == EPI_F32 ? e.ldo : sh.N;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tw[(4 * g + r) * 16 + c16] = v[r];
+    __builtin_amdgcn_wave_barrier();
+    const int row = 16 * mb + (lane >> 2);
+    const float4 o = *reinterpret_cast<const float4*>(tw + (lane >> 2) * 16 + 4 * (lane & 3));
+    if (row < sh.M) *reinterpret_cast<float4*>(base + (int64_t)row * ld + 16 * blk + 4 * (lane & 3)) = o;
+    __builtin_amdgcn_wave_barrier();
+    return;
+  }
+  if constexpr (KIND == EPI_ZIN) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * mb + 4 * g + r, col = 16 * blk + c16;
+      if (row < sh.M)
+        store_tiled<T>((T*)e.out_t, e.o_mtiles, row, sh.N + col, e.out_f[(int64_t)row * e.ldo + col] + v[r]);
+    }
+    return;
+  }
+  f32x4 vp;  // lane column c16 ^ 8
+#pragma unroll
+  for (int r = 0; r < 4; ++r) vp[r] = dpp_mov<DPP_ROR8>(v[r]);
+  if constexpr (sizeof(T) == 2 && KIND == EPI_SWIGLU) {
+    T* tt = reinterpret_cast<T*>(tw);
+    if (c16 < 8) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) tt[(4 * g + r) * 8 + c16] = ET<T>::from_f(silu_f(v[r]) * vp[r]);
+    }
+    __builtin_amdgcn_wave_barrier();
+    if (lane < 16) {
+      const int row = 16 * mb + lane;
+      const int4 o = *reinterpret_cast<const int4*>(tt + lane * 8);
+      if (row < sh.M) *reinterpret_cast<int4*>((T*)e.out_t + tiled_index<T>(e.o_mtiles, row, 8 * blk)) = o;
+    }
+    __builtin_amdgcn_wave_barrier();
+  } else if constexpr (KIND == EPI_QKV) {
+    T* tt = reinterpret_cast<T*>(tw);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if constexpr (sizeof(T) == 2)
+        tt[(4 * g + r) * 16 + c16] = ET<T>::from_f(qkv_value(e, blk, c16, v[r], vp[r], cs[r], sn[r]));
+      else if (16 * mb + 4 * g + r < sh.M)
+        qkv_store<T>(e, rm[4 * g + r], blk, c16, v[r], vp[r], cs[r], sn[r]);
+    }
+    if constexpr (sizeof(T) == 2) {
+      __builtin_amdgcn_wave_barrier();
+      if (lane < 32) {
+        const int4 o = *reinterpret_cast<const int4*>(tt + (lane & 15) * 16 + 8 * (lane >> 4));
+        if (16 * mb + (lane & 15) < sh.M) qkv_store16<T>(e, rm[lane & 15], blk, lane >> 4, o);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  } else {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = 16 * mb + 4 * g + r;
+      if (row < sh.M) epi_elem<T>(e, KIND, sh.N, sh.M, 0, row, blk, c16, v[r], vp[r]);
+    }
+  }
+}
+
 }  // namespace

@@ -18,7 +18,9 @@ enum { PACK_NATURAL = 0, PACK_QKV = 1, PACK_GU = 2 };
 // columns 8c + l (l < 8) and up columns 8c + l - 8 (l >= 8) in block c.  The
 // epilogue pairs lane columns l and l ^ 8.
 
-enum { EPI_F32 = 0, EPI_T = 1, EPI_SILU = 2, EPI_SWIGLU = 3, EPI_QKV = 4, EPI_PARTIAL = 5 };
+// EPI_ZIN (gemm_rows_takes launches only): the draft's residual add into the
+// second half of a head MLP's input, tiled out_t[row][N + col] = T(out_f[row][col] + v).
+enum { EPI_F32 = 0, EPI_T = 1, EPI_SILU = 2, EPI_SWIGLU = 3, EPI_QKV = 4, EPI_PARTIAL = 5, EPI_ZIN = 6 };
 
 struct GemmEpi {
   int kind = EPI_F32;
@@ -63,6 +65,10 @@ int gemm_pick_splits(int n_cols, int K, int dtype);
 // Partials [parts][M][N] that an EPI_PARTIAL launch writes: its slices, or 1
 // where a launch of many rows adds them (in slice order) itself.
 int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles);
+// Split launches of a few rows (kernels_gemm_rows.hip): all slices in one
+// workgroup per column block, the epilogue on the whole sum.
+bool gemm_rows_takes(int dtype, int M, int K, int splits, int kind);
+void launch_gemm_rows(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb);
 // Launches of many rows (kernels_gemm_wide.hip, bf16): the same sums on 2-D
 // output tiles.  sums_slices: the launch applies its epilogue to the whole
 // sum; otherwise a split launch writes one partial per slice.
@@ -256,11 +262,12 @@ void launch_advance(int dtype, const StepState& s, hipStream_t st);
 // n + level along each drafted node's path).  At level 0 rows
 // [B, B + B(K+1)) are the previous step's committed target-state entries
 // and rows [B + B(K+1), B + 2B(K+1)) their trigram entries.  Writes the
-// trigram inputs [rows][3d], rotary positions, encoder-memory offsets and Q rows.
+// trigram inputs [rows][3d], rotary positions, encoder-memory offsets and Q
+// rows, and h_last[b] into the first half of each query's row of zin (tiled).
 int draft_level_rows(const StepState& s, const DraftLevel& lv);
 void launch_draft_rows(int dtype, const StepState& s, const void* E, const DraftLevel& lv, void* tri_in,
-                       int tri_mtiles, int* pos, int64_t* kvoff, int* qrow, hipStream_t st);
-// zin[r] (tiled) = [h_last[b]; T(x[r] + sum_s parts[s][r])], r = b R + i,
+                       int tri_mtiles, int* pos, int64_t* kvoff, int* qrow, void* zin, int z_mtiles, hipStream_t st);
+// second half of zin[r] (tiled) = T(x[r] + sum_s parts[s][r]), r = b R + i,
 // parts [n_parts][B R][d]
 void launch_draft_finish(int dtype, const StepState& s, const DraftLevel& lv, const float* x, const float* parts,
                          int n_parts, void* zin, int z_mtiles, hipStream_t st);

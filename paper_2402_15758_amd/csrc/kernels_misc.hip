@@ -721,7 +721,7 @@ __device__ __forceinline__ int64_t enc_off(const StepState& s, int b, int stream
 
 template <typename T>
 __global__ void draft_rows_kernel(StepState s, const T* E, DraftLevel lv, T* tri_in, int tri_mtiles, int* pos,
-                                  int64_t* kvoff, int* qrow) {
+                                  int64_t* kvoff, int* qrow, T* zin, int z_mtiles) {
   const int r = blockIdx.x;
   const int B = s.B, K1 = s.K + 1, Q = B * lv.R;
   int b, p, node = -1, q = -1;
@@ -735,6 +735,11 @@ __global__ void draft_rows_kernel(StepState s, const T* E, DraftLevel lv, T* tri
     p = s.n[b] + lv.level;
     q = r;
     off = enc_off(s, b, 1, lv.level == 0 ? p : s.tree_slot0 + node);
+    // the query's head MLP input starts with the sequence's last state
+    constexpr int VEC = ET<T>::VEC;
+    const T* hl = (const T*)s.h_last + (int64_t)b * s.d;
+    for (int i = VEC * (blockIdx.y * blockDim.x + threadIdx.x); i < s.d; i += VEC * gridDim.y * blockDim.x)
+      st16(zin + tiled_index<T>(z_mtiles, r, i), ld16(hl + i));
   } else if (r < Q + B * K1) {
     const int i = r - Q;
     b = i / K1;
@@ -768,10 +773,8 @@ __global__ void draft_rows_kernel(StepState s, const T* E, DraftLevel lv, T* tri
 template <typename T>
 __global__ __launch_bounds__(256) void draft_finish_kernel(StepState s, DraftLevel lv, const float* x,
                                                            const float* parts, int n_parts, T* zin, int z_mtiles) {
-  const int r = blockIdx.x, b = r / lv.R, d = s.d, M = s.B * lv.R;
-  const T* hl = (const T*)s.h_last + (int64_t)b * d;
+  const int r = blockIdx.x, d = s.d, M = s.B * lv.R;
   for (int i = blockIdx.y * 256 + threadIdx.x; i < d; i += gridDim.y * 256) {
-    copy_tiled<T>(zin, z_mtiles, r, i, hl[i]);
     float pq[GEMM_MAX_SPLITS];  // every slice requested before the first is added
 #pragma unroll
     for (int q = 0; q < GEMM_MAX_SPLITS; ++q)
@@ -1081,15 +1084,15 @@ int draft_level_rows(const StepState& s, const DraftLevel& lv) {
 }
 
 void launch_draft_rows(int dtype, const StepState& s, const void* E, const DraftLevel& lv, void* tri_in,
-                       int tri_mtiles, int* pos, int64_t* kvoff, int* qrow, hipStream_t st) {
+                       int tri_mtiles, int* pos, int64_t* kvoff, int* qrow, void* zin, int z_mtiles, hipStream_t st) {
   const int pieces = 3 * s.d / (dtype == DT_BF16 ? 8 : 4);
   const dim3 grid(draft_level_rows(s, lv), (pieces + 255) / 256);
   if (dtype == DT_BF16)
     hipLaunchKernelGGL(draft_rows_kernel<bf16_t>, grid, dim3(256), 0, st, s, (const bf16_t*)E, lv,
-                       (bf16_t*)tri_in, tri_mtiles, pos, kvoff, qrow);
+                       (bf16_t*)tri_in, tri_mtiles, pos, kvoff, qrow, (bf16_t*)zin, z_mtiles);
   else
     hipLaunchKernelGGL(draft_rows_kernel<float>, grid, dim3(256), 0, st, s, (const float*)E, lv,
-                       (float*)tri_in, tri_mtiles, pos, kvoff, qrow);
+                       (float*)tri_in, tri_mtiles, pos, kvoff, qrow, (float*)zin, z_mtiles);
 }
 
 void launch_draft_finish(int dtype, const StepState& s, const DraftLevel& lv, const float* x, const float* parts,

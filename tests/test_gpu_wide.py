@@ -40,6 +40,29 @@ def test_rows_keep_their_bits_in_wide_launches(N, K):
         assert np.array_equal(y.view(np.uint32), ref[:M].view(np.uint32)), f"M={M}"
 
 
+# split reductions of a few rows (slices side by side in one workgroup): two,
+# four and eight slices, ragged classes, the activation rows from one piece to
+# the largest staging (7 rows of 8192 bf16), and one row more than fits
+@pytest.mark.parametrize("dtype,N,K,Ms", [
+    ("bf16", 192, 1024, (1, 16)), ("bf16", 64, 4096, (1, 3, 15)), ("bf16", 4096, 8192, (1, 7, 8)),
+    ("bf16", 1088, 5504, (2, 11)), ("f32", 256, 768, (1, 7, 16)), ("f32", 64, 2048, (1, 15, 16)),
+])
+def test_rows_keep_their_bits_in_launches_of_a_few_rows(dtype, N, K, Ms):
+    print(f"few rows {dtype} N={N} K={K}", flush=True)
+    torch.cuda.init()
+    rng = np.random.default_rng(N + K)
+    x = rng.standard_normal((32, K)).astype(np.float32)
+    w = rng.standard_normal((K, N)).astype(np.float32)
+    dt = B.CHIMERA_F32
+    if dtype == "bf16":
+        x, w = ((v.view(np.uint32) >> 16).astype(np.uint16) for v in (x, w))
+        dt = B.CHIMERA_BF16
+    ref = _gemm(dt, x, w)  # 32 rows: the streaming kernel and its finishing pass
+    for M in Ms:
+        y = _gemm(dt, x[:M].copy(), w)
+        assert np.array_equal(y.view(np.uint32), ref[:M].view(np.uint32)), f"M={M}"
+
+
 def _states(sess):
     """What two steps after the prefill show of every sequence."""
     out = [[] for _ in range(sess.batch)]
