@@ -101,6 +101,21 @@ __device__ __forceinline__ float row16_max(float v) {
   v = fmaxf(v, dpp_mov<DPP_MIRROR8>(v));
   return fmaxf(v, dpp_mov<DPP_MIRROR16>(v));
 }
+// the same reductions on ints, over all 64 lanes
+template <int CTRL>
+__device__ __forceinline__ int dpp_mov_i(int v) {
+  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
+}
+__device__ __forceinline__ int wave_min_i(int v) {
+  v = min(v, dpp_mov_i<DPP_XOR1>(v));
+  v = min(v, dpp_mov_i<DPP_XOR2>(v));
+  v = min(v, dpp_mov_i<DPP_MIRROR8>(v));
+  v = min(v, dpp_mov_i<DPP_MIRROR16>(v));
+  const auto p = __builtin_amdgcn_permlane16_swap((unsigned)v, (unsigned)v, false, false);
+  v = min((int)p[0], (int)p[1]);
+  const auto h = __builtin_amdgcn_permlane32_swap((unsigned)v, (unsigned)v, false, false);
+  return min((int)h[0], (int)h[1]);
+}
 // over all 64 lanes (call with every lane active)
 __device__ __forceinline__ float wave_sum(float v) { return rows_sum(row16_sum(v)); }
 __device__ __forceinline__ float wave_max(float v) { return rows_max(row16_max(v)); }

@@ -367,8 +367,10 @@ void verify_layers(chimera_ctx* c, const VerifyRows& r, hipStream_t st, bool tim
   const int dt = m->dt, d = cf.d_model, F = cf.d_ffn, H = cf.n_heads, hd = cf.head_dim;
   const int hdim = H * hd;
   const Gemm g{c, st, timed};
-  launch_embed(dt, r.tokens, m->embed, c->x, r.M, d, cf.vocab, st);
-  launch_attn_rows(r.n_b, r.page_table, kv->max_pages, kv->ps, kv->page_stride, hd, r.N, r.B, r.blk, c->rowtab, st);
+  if (r.blk != nullptr) {  // a step's verify setup has done both
+    launch_embed(dt, r.tokens, m->embed, c->x, r.M, d, cf.vocab, st);
+    launch_attn_rows(r.blk, r.B, r.page_table, kv->max_pages, kv->ps, kv->page_stride, hd, c->rowtab, st);
+  }
   int nparts = 0;
   for (int l = 0; l < cf.n_layers; ++l) {
     const BlockW& w = m->layers[l];
@@ -499,6 +501,8 @@ StepState make_state(chimera_ctx* c) {
   s.d_path = dm.path;
   s.tok_src = c->tok_src;
   s.tree_slot0 = kv->cap - ENC_TREE_SLOTS;
+  s.stamp_ring = c->stamp_ring;
+  s.stamp_count = c->stamp_count;
   return s;
 }
 
@@ -595,7 +599,7 @@ void run_draft(chimera_ctx* c, const StepState& s, hipStream_t st) {
     ed.out_f = c->htri;
     ed.ldo = d;
     ed.part = c->dparts;
-    ed.kind = gemm_rows_takes(dt, Q, F, gemm_pick_splits(d, F, dt), EPI_ZIN) ? EPI_ZIN : EPI_PARTIAL;
+    ed.kind = gemm_rows_takes(dt, Q, d / 16, F, gemm_pick_splits(d, F, dt), EPI_ZIN) ? EPI_ZIN : EPI_PARTIAL;
     g.run(c->hc, c->mt_q, Q, m->enc.wdown, d, F, ed);
     if (ed.kind == EPI_PARTIAL)
       launch_draft_finish(dt, s, lv, c->htri, c->dparts, gemm_partials(dt, Q, d, F, c->mt_q), c->zin, c->mt_q, st);
@@ -1299,18 +1303,12 @@ void enqueue_step(chimera_ctx* ctx, hipStream_t st) {
     }
     ctx->ev_created = true;
   }
-  // Phase timestamps: a one-lane kernel between phases writes the device
-  // wall clock.  They are part of every step (graph or eager), so turning
-  // profiling on times the same replayed graph that runs without it.
-  auto mark = [&](int idx, hipStream_t q) { launch_stamp(ctx->stamp_ring, ctx->stamp_count, idx, ctx->n, ctx->batch, q); };
   // the launch sequence of one step; every varying scalar lives in device memory
   auto enqueue = [&](hipStream_t q) {
     const Gemm gq{ctx, q, true};
     ctx->ev_used = 0;
-    mark(0, q);
     if (ctx->K > 0) run_draft(ctx, s, q);
-    mark(1, q);
-    launch_tree_setup(s, q);
+    launch_verify_setup(dt, s, m->embed, ctx->x, ctx->rowtab, q);
     const int M = ctx->batch * ctx->N;
     VerifyRows r{ctx->tree_tok, M, ctx->n, kv->page_table, ctx->tree.depth, ctx->tree.path, ctx->N, ctx->D,
                  ctx->batch, ctx->mt_v, nullptr};
@@ -1325,14 +1323,11 @@ void enqueue_step(chimera_ctx* ctx, hipStream_t st) {
                            ctx->t_seed, ctx->t_lse, ctx->t_H, ctx->t_sample, q);
     else
       launch_argmax(ctx->logits, M, V, ctx->amax, q);
-    mark(2, q);
-    launch_accept(dt, s, q);
     if (ctx->cc_side) launch_kv_snapshot(dt, s, kv->pool, cf.n_layers, kv->layer_stride, ctx->cc_side, q);
-    launch_compact(dt, s, kv->pool, cf.n_layers, kv->layer_stride, q);
+    launch_step_end(dt, s, kv->pool, cf.n_layers, kv->layer_stride, q);
     if (ctx->cc_side)
       launch_kv_check(dt, s, kv->pool, cf.n_layers, kv->layer_stride, ctx->cc_side, ctx->cc_counts, q);
-    launch_advance(dt, s, q);
-    mark(3, q);
+    launch_stamp(s, q);
   };
   if (use_graph) {
     if (ctx->gexec == nullptr || ctx->graph_stream != st || ctx->graph_batch != ctx->batch) {

@@ -67,7 +67,7 @@ int gemm_pick_splits(int n_cols, int K, int dtype);
 int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles);
 // Split launches of a few rows (kernels_gemm_rows.hip): all slices in one
 // workgroup per column block, the epilogue on the whole sum.
-bool gemm_rows_takes(int dtype, int M, int K, int splits, int kind);
+bool gemm_rows_takes(int dtype, int M, int nbc, int K, int splits, int kind);
 void launch_gemm_rows(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb);
 // Launches of many rows (kernels_gemm_wide.hip, bf16): the same sums on 2-D
 // output tiles.  sums_slices: the launch applies its epilogue to the whole
@@ -131,7 +131,7 @@ struct TreeAttnArgs {
   void* out;                // tiled [B*N][H*hd] with o_mtiles tiles
   int o_mtiles;
   int B;
-  const int64_t* rowtab;    // [B][TREE_ATTN_TAIL_ROWS] from launch_attn_rows
+  const int64_t* rowtab;    // [B][TREE_ATTN_TAIL_ROWS] window rows
   // Prefill: B query blocks of prompt positions in place of B trees (a chain
   // each); one partial per query, part_o [rows][H][hd], part_ml [rows][H][2].
   const PrefillBlock* blk;  // nullptr: decode
@@ -147,9 +147,10 @@ constexpr int TREE_ATTN_WINDOW = 16;
 // W + j the slot of tree node j.
 constexpr int TREE_ATTN_TAIL_ROWS = TREE_ATTN_WINDOW + 64;
 // rowtab[b][rr] = page-resolved element offset (head and layer excluded) of
-// window row rr, written once per verify pass for all layers.
-void launch_attn_rows(const int* n_b, const int* page_table, int max_pages, int ps, int64_t page_stride, int hd,
-                      int N, int B, const PrefillBlock* blk, int64_t* rowtab, hipStream_t st);
+// window row rr, written once per pass for all layers: by the verify setup of
+// a step, by this launch for the blocks of a prefill chunk.
+void launch_attn_rows(const PrefillBlock* blk, int n_blk, const int* page_table, int max_pages, int ps,
+                      int64_t page_stride, int hd, int64_t* rowtab, hipStream_t st);
 
 // Query row r = b * R + i of draft level `level` is draft-tree node
 // nodes[i] of sequence b, at trigram position n_b + level.  Its keys, in
@@ -227,6 +228,8 @@ struct StepState {
   const uint8_t* d_path;    // [64][64] draft-tree node at each depth on the root->u path
   const int* tok_src;       // [N] verify node -> the cand row holding its token (rank t_rank)
   int tree_slot0;           // stream-1 slot of draft-tree node 0 in the encoder memory
+  unsigned long long* stamp_ring;  // phase timestamps (below)
+  unsigned int* stamp_count;
 };
 // One draft level: R drafted nodes per sequence, s.d_nodes[off .. off + R).
 // Query rows r = b * R + i; at level 0 (R = 1) the prologue rows follow.
@@ -246,9 +249,11 @@ void launch_argmax(const float* logits, int M, int V, int* amax, hipStream_t st)
 // cand[b][node] (forced as set up in s).  scratch: [B*R][32][8] values and ids.
 void launch_topk(const float* logits, int64_t ld, const StepState& s, const DraftLevel& lv, float* scratch_v,
                  int* scratch_i, hipStream_t st);
-void launch_tree_setup(const StepState& s, hipStream_t st);
-void launch_accept(int dtype, const StepState& s, hipStream_t st);
-void launch_compact(int dtype, const StepState& s, void* pool, int n_layers, int64_t layer_stride, hipStream_t st);
+// Start of the verify pass: tree tokens, row descriptors, window rows and the
+// embeddings of all nodes into x [B N][d].
+void launch_verify_setup(int dtype, const StepState& s, const void* E, float* x, int64_t* rowtab, hipStream_t st);
+// End of a step: acceptance, KV compaction of all layers, state advance.
+void launch_step_end(int dtype, const StepState& s, void* pool, int n_layers, int64_t layer_stride, hipStream_t st);
 // Compaction check: the tree's K/V rows of every layer copied to side
 // [layer][kv][B][N][H*hd] before compaction, compared with the accepted
 // path's slots after it (counts[0] += rows, counts[1] += differing chunks).
@@ -256,7 +261,6 @@ void launch_kv_snapshot(int dtype, const StepState& s, const void* pool, int n_l
                         void* side, hipStream_t st);
 void launch_kv_check(int dtype, const StepState& s, const void* pool, int n_layers, int64_t layer_stride,
                      const void* side, unsigned long long* counts, hipStream_t st);
-void launch_advance(int dtype, const StepState& s, hipStream_t st);
 
 // Rows of draft level lv.  Rows [0, B R) are the queries (trigram position
 // n + level along each drafted node's path).  At level 0 rows
@@ -324,8 +328,9 @@ void launch_prefill_finish(const StepState& s, const PrefillEnds& e, const int* 
 // Every step writes one ring slot of STAMP_WORDS words: the device wall clock
 // (hipDeviceAttributeWallClockRate kHz) at step start (0), draft end (1),
 // verify end (2) and step end (3), and the step's summed committed length
-// (4).  A stamp runs after every earlier kernel of the stream has finished;
-// stamp 3 advances the step counter.
+// (4).  Stamps 0 to 2 are taken by the first kernel of each phase as it
+// starts, when every earlier kernel of the stream has finished; stamp 3 is a
+// launch of its own and advances the step counter.
 constexpr int STAMP_RING = 4096;
 constexpr int STAMP_WORDS = 8;
-void launch_stamp(unsigned long long* ring, unsigned int* counter, int idx, const int* n_b, int B, hipStream_t st);
+void launch_stamp(const StepState& s, hipStream_t st);

@@ -17,6 +17,7 @@
 // The decomposition depends on P_u alone, so a query gets bit-identical
 // results whether it is a node of a 64-node tree or the single query of a
 // plain autoregressive step at the same position.
+#include "attn_rows.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -57,22 +58,13 @@ constexpr int MAX_NODES = 64;
 static_assert(WIN + MAX_NODES == TREE_ATTN_TAIL_ROWS, "window rows");
 static_assert(WIN == 16, "the window pass maps four lanes to each window key");
 
-// Page-resolved offsets of the window rows: entry k < WIN is position
-// n - WIN + k (committed), entry WIN + j the slot of tree node j (position
-// n + j); entries before position 0 or past the tree are zero.
-__global__ void attn_rows_kernel(const int* __restrict__ n_b, const int* __restrict__ page_table, int max_pages,
-                                 int ps, int64_t page_stride, int hd, int N, const PrefillBlock* __restrict__ blk,
-                                 int64_t* __restrict__ rowtab) {
-  const int b = blockIdx.x;
-  const PrefillBlock pb = blk ? blk[b] : PrefillBlock{0, n_b[b], N, b};
-  const int n = pb.n;
-  for (int rr = threadIdx.x; rr < TREE_ATTN_TAIL_ROWS; rr += blockDim.x) {
-    const int p = rr < WIN ? n - WIN + rr : n + rr - WIN;
-    int64_t off = 0;
-    if (p >= 0 && (rr < WIN || rr - WIN < pb.count))
-      off = (int64_t)page_table[(int64_t)pb.seq * max_pages + p / ps] * page_stride + (int64_t)(p % ps) * hd;
-    rowtab[(int64_t)b * TREE_ATTN_TAIL_ROWS + rr] = off;
-  }
+// The window rows of a prefill chunk's blocks (a decode step's come with its
+// verify setup).
+__global__ void attn_rows_kernel(const int* __restrict__ page_table, int max_pages, int ps, int64_t page_stride, int hd,
+                                 const PrefillBlock* __restrict__ blk, int64_t* __restrict__ rowtab) {
+  const PrefillBlock pb = blk[blockIdx.x];
+  window_rows(page_table + (int64_t)pb.seq * max_pages, pb.n, pb.count, ps, page_stride, hd,
+              rowtab + (int64_t)blockIdx.x * TREE_ATTN_TAIL_ROWS);
 }
 
 // ---------------------------------------------------------------------------
@@ -716,10 +708,10 @@ void enc_attn_go(const EncAttnArgs& a, hipStream_t st) {
 
 }  // namespace
 
-void launch_attn_rows(const int* n_b, const int* page_table, int max_pages, int ps, int64_t page_stride, int hd,
-                      int N, int B, const PrefillBlock* blk, int64_t* rowtab, hipStream_t st) {
-  hipLaunchKernelGGL(attn_rows_kernel, dim3(B), dim3(TREE_ATTN_TAIL_ROWS), 0, st, n_b, page_table, max_pages, ps,
-                     page_stride, hd, N, blk, rowtab);
+void launch_attn_rows(const PrefillBlock* blk, int n_blk, const int* page_table, int max_pages, int ps,
+                      int64_t page_stride, int hd, int64_t* rowtab, hipStream_t st) {
+  hipLaunchKernelGGL(attn_rows_kernel, dim3(n_blk), dim3(TREE_ATTN_TAIL_ROWS), 0, st, page_table, max_pages, ps,
+                     page_stride, hd, blk, rowtab);
 }
 
 void launch_tree_attn(int dtype, const TreeAttnArgs& a, hipStream_t st) {

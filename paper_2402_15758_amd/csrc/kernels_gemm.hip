@@ -551,7 +551,6 @@ int gemm_pick_splits(int n_cols, int K, int dtype) {
 }
 
 int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles) {
-  if (gemm_rows_takes(dtype, M, K, gemm_pick_splits(n_cols, K, dtype), EPI_PARTIAL)) return 1;
   if (gemm_wide_takes(dtype, M, K, x_mtiles) && gemm_wide_sums_slices(M, n_cols / 16, EPI_PARTIAL)) return 1;
   return gemm_pick_splits(n_cols, K, dtype);
 }
@@ -559,7 +558,7 @@ int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles) {
 void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start,
                  hipEvent_t ev_stop) {
   if (s.M <= 0) return;
-  if (gemm_rows_takes(dtype, s.M, s.K, s.splits, e.kind)) {
+  if (gemm_rows_takes(dtype, s.M, gemm_blocks(s), s.K, s.splits, e.kind)) {
     launch_gemm_rows(dtype, s, e, st, ev_start, ev_stop);
     return;
   }

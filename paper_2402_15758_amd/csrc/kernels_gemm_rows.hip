@@ -1,9 +1,11 @@
 // Split-K GEMMs of a few rows in one launch (M <= 16, narrow matrices: the
-// draft's trigram encoder, O and down projections and head MLPs, and greedy
-// decoding's O and down).  The streaming kernel runs one workgroup per
-// reduction slice and leaves the slices to a finishing launch or to its
-// consumer; with a few rows that second pass over some hundred KiB costs as
-// much as a fifth of the product (3.8 us next to 15-20 us at 7B width).
+// draft's trigram encoder, down projection and head MLPs).  The streaming
+// kernel runs one workgroup per
+// reduction slice and leaves the slices to a finishing launch: with a few rows
+// a pass over some hundred KiB that costs as much as a fifth of the product
+// (3.8 us next to 15-20 us at 7B width).  Where the consumer adds the slices
+// anyway (the norms after O and down) it stays the faster one, 11.7 us against
+// 13.1 a launch in greedy decoding at 7B width.
 //
 // Here a workgroup owns one 16-column block and the whole reduction: four
 // waves per slice (up to four slices side by side, 16 waves), each summing the
@@ -110,7 +112,6 @@ void go_waves(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t e
 template <typename T>
 void go_kind(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
   switch (e.kind) {
-    case EPI_PARTIAL: go_waves<T, EPI_PARTIAL>(s, e, st, ea, eb); break;
     case EPI_F32: go_waves<T, EPI_F32>(s, e, st, ea, eb); break;
     case EPI_ZIN: go_waves<T, EPI_ZIN>(s, e, st, ea, eb); break;
     default: go_waves<T, EPI_SILU>(s, e, st, ea, eb); break;
@@ -119,9 +120,13 @@ void go_kind(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea
 
 }  // namespace
 
-bool gemm_rows_takes(int dtype, int M, int K, int splits, int kind) {
-  return splits > 1 && splits <= GEMM_MAX_SPLITS && M <= 16 &&
-         (kind == EPI_PARTIAL || kind == EPI_F32 || kind == EPI_SILU || kind == EPI_ZIN) &&
+bool gemm_rows_takes(int dtype, int M, int nbc, int K, int splits, int kind) {
+  // One workgroup per CU streams its block at the same rate as all others, so
+  // a last round that is mostly empty costs more than the finishing launch
+  // (320 blocks of K = 15360: 33 us against 28 + 4).
+  const int rounds = (nbc + 255) / 256;
+  return (rounds == 1 || 10 * (rounds * 256 - nbc) <= nbc) && splits > 1 && splits <= GEMM_MAX_SPLITS && M <= 16 &&
+         (kind == EPI_F32 || kind == EPI_SILU || kind == EPI_ZIN) &&
          (int64_t)M * K * (dtype == DT_BF16 ? 2 : 4) <= MAX_LDS_X;
 }
 

@@ -1,19 +1,33 @@
 // Decode-state kernels: embedding gather, RMSNorm with fused residual add,
 // argmax and top-s selection, tree assembly, greedy acceptance, in-place KV
 // compaction, state advance, and the row setup of the draft and prefill.
+#include "attn_rows.h"
 #include "common.h"
 #include "kernels.h"
 
 namespace {
 
 
+// One lane stores the GPU's constant-rate wall clock into the current step's
+// ring slot.  Kernels of a stream run one after another, so the first kernel
+// of a phase records when the last kernel of the phase before has finished,
+// and the four stamps of a step see the same counter.
+__device__ __forceinline__ void stamp(const StepState& s, int idx) {
+  const unsigned int c = *s.stamp_count;
+  unsigned long long* slot = s.stamp_ring + (size_t)(c % STAMP_RING) * STAMP_WORDS;
+  slot[idx] = __builtin_amdgcn_s_memrealtime();
+  if (idx == 0) {
+    unsigned long long sum = 0;
+    for (int b = 0; b < s.B; ++b) sum += (unsigned long long)s.n[b];
+    slot[4] = sum;
+  }
+  if (idx == 3) *s.stamp_count = c + 1;
+}
+
+// Embedding row of token t as floats (256 threads).
 template <typename T>
-__global__ void embed_kernel(const int* __restrict__ tokens, const T* __restrict__ E, float* __restrict__ x, int d,
-                             int V) {
-  const int r = blockIdx.x;
-  const int t = min(max(tokens[r], 0), V - 1);
-  const T* e = E + (int64_t)t * d;
-  float* xr = x + (int64_t)r * d;
+__device__ __forceinline__ void embed_row(int t, const T* __restrict__ E, float* __restrict__ xr, int d, int V) {
+  const T* e = E + (int64_t)min(max(t, 0), V - 1) * d;
   constexpr int VEC = ET<T>::VEC, U = 4;  // 16-byte pieces, U per thread requested at once
   const int pieces = d / VEC;
   for (int p0 = threadIdx.x; p0 < pieces; p0 += U * 256) {
@@ -30,6 +44,13 @@ __global__ void embed_kernel(const int* __restrict__ tokens, const T* __restrict
     }
   }
   for (int i = pieces * VEC + threadIdx.x; i < d; i += 256) xr[i] = ET<T>::to_f(e[i]);  // d % VEC tail
+}
+
+template <typename T>
+__global__ __launch_bounds__(256) void embed_kernel(const int* __restrict__ tokens, const T* __restrict__ E,
+                                                    float* __restrict__ x, int d, int V) {
+  const int r = blockIdx.x;
+  embed_row<T>(tokens[r], E, x + (int64_t)r * d, d, V);
 }
 
 // Fixed-order block sum: wave butterflies, then the waves in order.
@@ -148,43 +169,28 @@ __global__ __launch_bounds__(1024) void rmsnorm_kernel(float* __restrict__ x, co
 // (value, id) order: larger value first, then lower id.
 __device__ __forceinline__ bool better(float v, int i, float bv, int bi) { return v > bv || (v == bv && i < bi); }
 
+// Best (value, id) over the 64 lanes of a wave, on every lane: the largest
+// value, then the lowest id among the lanes that hold it.  Both reductions run
+// on the VALU (DPP and lane swaps): twelve short steps, where a butterfly of
+// pairs through the LDS crossbar is twelve round trips of over 100 cycles.
+__device__ __forceinline__ void wave_best(float& v, int& i) {
+  const float bv = wave_max(v);
+  i = wave_min_i(v == bv ? i : 0x7fffffff);
+  v = bv;
+}
+
 __device__ __forceinline__ void block_best(float& v, int& i, float* shv, int* shi) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    const float ov = __shfl_xor(v, m);
-    const int oi = __shfl_xor(i, m);
-    if (better(ov, oi, v, i)) {
-      v = ov;
-      i = oi;
-    }
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  wave_best(v, i);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, waves = blockDim.x >> 6;
   __syncthreads();
   if (lane == 0) {
     shv[wave] = v;
     shi[wave] = i;
   }
   __syncthreads();
-  v = shv[0];
-  i = shi[0];
-  for (int w = 1; w < (int)(blockDim.x >> 6); ++w)
-    if (better(shv[w], shi[w], v, i)) {
-      v = shv[w];
-      i = shi[w];
-    }
-}
-
-// Best (value, id) over the 64 lanes of a wave, on every lane.
-__device__ __forceinline__ void wave_best(float& v, int& i) {
-#pragma unroll
-  for (int m = 32; m >= 1; m >>= 1) {
-    const float ov = __shfl_xor(v, m);
-    const int oi = __shfl_xor(i, m);
-    if (better(ov, oi, v, i)) {
-      v = ov;
-      i = oi;
-    }
-  }
+  v = lane < waves ? shv[lane] : -CH_INF;
+  i = lane < waves ? shi[lane] : 0x7fffffff;
+  wave_best(v, i);
 }
 
 __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ logits, int V, int* __restrict__ amax) {
@@ -224,6 +230,9 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
 // Stage 1: TOPK_SPLIT workgroups per sequence keep the best S ids of their
 // slice (excluding the reference id); stage 2 merges them.
 constexpr int TOPK_SPLIT = 32;
+// Up to this vocabulary one workgroup scans a row and writes the list itself
+// (at 1024 entries the merge launch is half of the time).
+constexpr int TOPK_ONE = 4096;
 constexpr int SMAX = 8;
 
 __device__ __forceinline__ int forced_ref(const StepState& s, int b, int level, int V, bool* ok) {
@@ -247,7 +256,8 @@ __global__ __launch_bounds__(256) void topk_partial_kernel(const float* __restri
   bool ok;
   const int excl = forced_ref(s, b, level, V, &ok);
   const float* z = logits + (int64_t)r * ld;
-  const int lo = (int)((int64_t)V * split / TOPK_SPLIT), hi = (int)((int64_t)V * (split + 1) / TOPK_SPLIT);
+  const int nsplit = gridDim.x;
+  const int lo = (int)((int64_t)V * split / nsplit), hi = (int)((int64_t)V * (split + 1) / nsplit);
   float lv[SMAX];
   int li[SMAX];
 #pragma unroll
@@ -314,6 +324,9 @@ __global__ __launch_bounds__(256) void topk_partial_kernel(const float* __restri
     cv = shv[(lane / S) * SMAX + lane % S];
     ci = shi[(lane / S) * SMAX + lane % S];
   }
+  const int node = nsplit == 1 ? s.d_nodes[dl.off + r % dl.R] : 0;
+  int* out = s.cand + ((int64_t)b * 64 + node) * 8 + (ok ? 1 : 0);  // a forced list starts with the reference
+  if (nsplit == 1 && ok && lane == 0) out[-1] = excl;
   for (int q = 0; q < S; ++q) {
     float bv = cv;
     int bi = ci;
@@ -322,7 +335,9 @@ __global__ __launch_bounds__(256) void topk_partial_kernel(const float* __restri
       cv = -CH_INF;
       ci = 0x7fffffff;
     }
-    if (lane == 0) {
+    if (nsplit == 1) {
+      if (lane == 0 && q + (ok ? 1 : 0) < S) out[q] = bi < V ? bi : 0;
+    } else if (lane == 0) {
       pv[((int64_t)r * TOPK_SPLIT + split) * SMAX + q] = bv;
       pi[((int64_t)r * TOPK_SPLIT + split) * SMAX + q] = bi;
     }
@@ -368,15 +383,7 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(StepState s, DraftLevel 
       }
     float wv = bv;
     int wi = bi;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-      const float ov = __shfl_xor(wv, m);
-      const int oi = __shfl_xor(wi, m);
-      if (better(ov, oi, wv, wi)) {
-        wv = ov;
-        wi = oi;
-      }
-    }
+    wave_best(wv, wi);
     if (bq >= 0 && bi == wi) {
 #pragma unroll
       for (int q = 0; q < PER; ++q)
@@ -387,11 +394,18 @@ __global__ __launch_bounds__(64) void topk_merge_kernel(StepState s, DraftLevel 
   }
 }
 
-__global__ void tree_setup_kernel(StepState s) {
-  const int b = blockIdx.x, u = threadIdx.x;
-  if (u >= s.N) return;
+// Start of the verify pass: workgroup (u, b) gives node u of sequence b its
+// token, its row descriptors and its embedding; workgroup (0, b) also resolves
+// the attention window's rows.  One launch where tree assembly, row table,
+// embedding and phase stamp were four of 2-3 us each.
+template <typename T>
+__global__ __launch_bounds__(256) void verify_setup_kernel(StepState s, const T* E, float* x, int64_t* rowtab) {
+  const int u = blockIdx.x, b = blockIdx.y;
+  if (u == 0 && b == 0 && threadIdx.x == 0) {
+    if (s.K == 0) stamp(s, 0);  // no draft before it
+    stamp(s, 1);
+  }
   const int n = s.n[b];
-  const int dep = s.t_depth[u];
   int t;
   if (u == 0)
     t = s.tok[(int64_t)b * s.tok_stride + n];
@@ -400,15 +414,18 @@ __global__ void tree_setup_kernel(StepState s) {
   else
     t = s.cand[((int64_t)b * 64 + s.tok_src[u]) * 8 + s.t_rank[u]];
   const int row = b * s.N + u;
-  s.tree_tok[row] = t;
-  const int slot = n + u;
-  s.v_pos[row] = n + dep;
-  s.v_qrow[row] = row;
-  s.v_kvoff[row] =
-      (int64_t)s.page_table[(int64_t)b * s.max_pages + slot / s.ps] * s.page_stride + (int64_t)(slot % s.ps) * s.hd;
+  const int* ptab = s.page_table + (int64_t)b * s.max_pages;
+  if (threadIdx.x == 0) {
+    s.tree_tok[row] = t;
+    const int slot = n + u;
+    s.v_pos[row] = n + s.t_depth[u];
+    s.v_qrow[row] = row;
+    s.v_kvoff[row] = (int64_t)ptab[slot / s.ps] * s.page_stride + (int64_t)(slot % s.ps) * s.hd;
+  }
+  if (u == 0) window_rows(ptab, n, s.N, s.ps, s.page_stride, s.hd, rowtab + (int64_t)b * TREE_ATTN_TAIL_ROWS);
+  embed_row<T>(t, E, x + (int64_t)row * s.d, s.d, s.V);
 }
 
-// Greedy acceptance, one wave per sequence, lane = tree node.
 __device__ __forceinline__ double readlane_f64(double x, int lane) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(x);
   const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)u, lane);
@@ -416,8 +433,10 @@ __device__ __forceinline__ double readlane_f64(double x, int lane) {
   return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
 }
 
-__global__ void accept_kernel(StepState s) {
-  const int b = blockIdx.x, u = threadIdx.x;
+constexpr int MAX_PATH = 9;  // a path has at most 8 nodes below the root
+// The accepted path of sequence b: its length, nodes and bonus token, on the
+// lanes of one wave (u: lane).  write: also publish them.
+__device__ __forceinline__ int accept_path(const StepState& s, int b, int u, bool write, int* nodes) {
   const bool valid = u < s.N;
   const int row = b * s.N + (valid ? u : 0);
   const int tok_u = s.tree_tok[row];
@@ -478,14 +497,23 @@ __global__ void accept_kernel(StepState s) {
   const int K1 = s.K + 1;
   if (valid && ((path >> u) & 1ull)) {
     const int idx = __popcll(path & ((1ull << u) - 1ull));
-    s.out_nodes[b * K1 + idx] = u;
-    if (idx >= 1) s.out_tok[b * K1 + idx - 1] = tok_u;
+    nodes[idx] = u;
+    if (idx >= 1) nodes[MAX_PATH + idx - 1] = tok_u;
+    if (write) {
+      s.out_nodes[b * K1 + idx] = u;
+      if (idx >= 1) s.out_tok[b * K1 + idx - 1] = tok_u;
+    }
   }
   if (u == 0) {
-    s.out_tok[b * K1 + L - 1] = bonus;
-    s.out_len[b] = L;
+    nodes[MAX_PATH + L - 1] = bonus;
+    if (write) {
+      s.out_tok[b * K1 + L - 1] = bonus;
+      s.out_len[b] = L;
+    }
   }
+  return L;
 }
+
 
 __device__ __forceinline__ unsigned long long splitmix64_d(unsigned long long x) {
   unsigned long long z = x + 0x9e3779b97f4a7c15ull;
@@ -566,33 +594,6 @@ __global__ __launch_bounds__(1024) void typical_stats_kernel(const float* __rest
   }
 }
 
-// In-place compaction of the accepted path: slot n+d <- slot n+path[d], for
-// d = 1..L-1 in increasing order (sources are never below their
-// destination, so no source is overwritten before it is read).
-template <typename T>
-__global__ __launch_bounds__(256) void compact_kernel(StepState s, T* pool, int64_t layer_stride) {
-  const int layer = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
-  const int L = s.out_len[b];
-  const int n = s.n[b];
-  const int K1 = s.K + 1;
-  constexpr int VEC = ET<T>::VEC;
-  T* base = pool + (int64_t)layer * layer_stride + (int64_t)kv * s.H * s.ps * s.hd;
-  const int* ptab = s.page_table + (int64_t)b * s.max_pages;
-  const int nvec = s.H * s.hd / VEC;
-  for (int dd = 1; dd < L; ++dd) {
-    const int src = n + s.out_nodes[b * K1 + dd];
-    const int dst = n + dd;
-    if (src == dst) continue;
-    const int64_t sb = (int64_t)ptab[src / s.ps] * s.page_stride + (int64_t)(src % s.ps) * s.hd;
-    const int64_t db = (int64_t)ptab[dst / s.ps] * s.page_stride + (int64_t)(dst % s.ps) * s.hd;
-    for (int e = threadIdx.x; e < nvec; e += 256) {
-      const int h = (e * VEC) / s.hd, dim = (e * VEC) % s.hd;
-      const int64_t ho = (int64_t)h * s.ps * s.hd + dim;
-      st16(base + db + ho, ld16(base + sb + ho));
-    }
-  }
-}
-
 // Compaction check (debug mode).  Before compaction: node u's K or V row of
 // every layer (slot n+u, all heads) is copied to
 // side[((layer * 2 + kv) * B + b) * N + u][H * hd].  After compaction: slot
@@ -624,7 +625,7 @@ __global__ __launch_bounds__(256) void kv_check_kernel(StepState s, const T* poo
   __shared__ unsigned int bad;
   const int layer = blockIdx.x, kv = blockIdx.y, b = blockIdx.z;
   const int L = s.out_len[b];
-  const int n = s.n[b];
+  const int n = s.v_pos[b * s.N];  // the step's committed length; s.n has moved on
   const int K1 = s.K + 1;
   constexpr int VEC = ET<T>::VEC;
   const T* base = pool + (int64_t)layer * layer_stride + (int64_t)kv * s.H * s.ps * s.hd;
@@ -653,30 +654,62 @@ __global__ __launch_bounds__(256) void kv_check_kernel(StepState s, const T* poo
   }
 }
 
-// Workgroup (b, idx) moves accepted row idx of sequence b into the encoder
-// prologue rows (and h_last for the last one); workgroup (b, 0) also commits
-// the tokens and advances n.
+// End of a step: acceptance, compaction and state advance of every sequence in
+// one launch (they were three, with a stamp before them).  Grid (2 layers +
+// K + 1, B); every workgroup works out its sequence's accepted path by itself.
+//   * x < 2 layers: in-place compaction of layer x / 2's K or V: slot n+d <-
+//     slot n+path[d] for d = 1..L-1 in increasing order (sources are never
+//     below their destination, so none is overwritten before it is read);
+//   * the others: accepted row idx into the encoder prologue rows (and h_last
+//     for the last one); idx 0 also publishes the path, commits the tokens and
+//     advances n -- the committed length the others use is the root's position,
+//     which only the next step rewrites.
 template <typename T>
-__global__ __launch_bounds__(256) void advance_kernel(StepState s) {
-  const int b = blockIdx.x, idx = blockIdx.y;
-  const int L = s.out_len[b];
-  const int K1 = s.K + 1;
-  const int d = s.d;
-  if (idx < L) {
-    const int node = s.out_nodes[b * K1 + idx];
-    const T* src = (const T*)s.hl + (int64_t)(b * s.N + node) * d;
-    T* dst = (T*)s.pro_h + ((int64_t)b * K1 + idx) * d;
-    T* hl = idx == L - 1 ? (T*)s.h_last + (int64_t)b * d : nullptr;
-    for (int i = threadIdx.x; i < d; i += 256) {
-      const T v = src[i];
-      dst[i] = v;
-      if (hl) hl[i] = v;
+__global__ __launch_bounds__(256) void step_end_kernel(StepState s, T* pool, int n_layers, int64_t layer_stride) {
+  __shared__ int nodes[2 * MAX_PATH];  // path nodes, then accepted tokens and bonus
+  __shared__ int len;
+  const int b = blockIdx.y, part = blockIdx.x - 2 * n_layers;
+  if (blockIdx.x == 0 && b == 0 && threadIdx.x == 0) stamp(s, 2);
+  const int n = s.v_pos[b * s.N];
+  if (threadIdx.x < 64) {
+    const int L = accept_path(s, b, threadIdx.x, part == 0, nodes);
+    if (threadIdx.x == 0) len = L;
+  }
+  __syncthreads();
+  const int L = len;
+  constexpr int VEC = ET<T>::VEC;
+  if (part < 0) {
+    const int layer = blockIdx.x / 2, kv = blockIdx.x % 2;
+    T* base = pool + (int64_t)layer * layer_stride + (int64_t)kv * s.H * s.ps * s.hd;
+    const int* ptab = s.page_table + (int64_t)b * s.max_pages;
+    const int nvec = s.H * s.hd / VEC;
+    for (int dd = 1; dd < L; ++dd) {
+      const int src = n + nodes[dd];
+      const int dst = n + dd;
+      if (src == dst) continue;
+      const int64_t sb = (int64_t)ptab[src / s.ps] * s.page_stride + (int64_t)(src % s.ps) * s.hd;
+      const int64_t db = (int64_t)ptab[dst / s.ps] * s.page_stride + (int64_t)(dst % s.ps) * s.hd;
+      for (int e = threadIdx.x; e < nvec; e += 256) {
+        const int h = (e * VEC) / s.hd, dim = (e * VEC) % s.hd;
+        const int64_t ho = (int64_t)h * s.ps * s.hd + dim;
+        st16(base + db + ho, ld16(base + sb + ho));
+      }
+    }
+    return;
+  }
+  const int K1 = s.K + 1, d = s.d;
+  if (part < L) {
+    const T* src = (const T*)s.hl + (int64_t)(b * s.N + nodes[part]) * d;
+    T* dst = (T*)s.pro_h + ((int64_t)b * K1 + part) * d;
+    T* hl = part == L - 1 ? (T*)s.h_last + (int64_t)b * d : nullptr;
+    for (int i = VEC * threadIdx.x; i < d; i += VEC * 256) {
+      const int4 v = ld16(src + i);
+      st16(dst + i, v);
+      if (hl) st16(hl + i, v);
     }
   }
-  if (idx != 0) return;
-  const int n = s.n[b];
-  if (threadIdx.x < L) s.tok[(int64_t)b * s.tok_stride + n + 1 + threadIdx.x] = s.out_tok[b * K1 + threadIdx.x];
-  __syncthreads();
+  if (part != 0) return;
+  if (threadIdx.x < L) s.tok[(int64_t)b * s.tok_stride + n + 1 + threadIdx.x] = nodes[MAX_PATH + threadIdx.x];
   if (threadIdx.x == 0) {
     s.pro_base[b] = n;
     s.pro_count[b] = L;
@@ -724,6 +757,7 @@ __global__ void draft_rows_kernel(StepState s, const T* E, DraftLevel lv, T* tri
                                   int64_t* kvoff, int* qrow, T* zin, int z_mtiles) {
   const int r = blockIdx.x;
   const int B = s.B, K1 = s.K + 1, Q = B * lv.R;
+  if (lv.level == 0 && r == 0 && blockIdx.y == 0 && threadIdx.x == 0) stamp(s, 0);
   int b, p, node = -1, q = -1;
   int64_t off;
   bool valid = true, want_tri = true;
@@ -1022,14 +1056,20 @@ void launch_argmax(const float* logits, int M, int V, int* amax, hipStream_t st)
 void launch_topk(const float* logits, int64_t ld, const StepState& s, const DraftLevel& lv, float* scratch_v,
                  int* scratch_i, hipStream_t st) {
   const int Q = s.B * lv.R;
-  hipLaunchKernelGGL(topk_partial_kernel, dim3(TOPK_SPLIT, Q), dim3(256), 0, st, logits, ld, s, lv, scratch_v,
+  const bool one = s.V <= TOPK_ONE;
+  hipLaunchKernelGGL(topk_partial_kernel, dim3(one ? 1 : TOPK_SPLIT, Q), dim3(256), 0, st, logits, ld, s, lv, scratch_v,
                      scratch_i);
+  if (one) return;
   hipLaunchKernelGGL(topk_merge_kernel, dim3(Q), dim3(64), 0, st, s, lv, (const float*)scratch_v,
                      (const int*)scratch_i);
 }
 
-void launch_tree_setup(const StepState& s, hipStream_t st) {
-  hipLaunchKernelGGL(tree_setup_kernel, dim3(s.B), dim3(64), 0, st, s);
+void launch_verify_setup(int dtype, const StepState& s, const void* E, float* x, int64_t* rowtab, hipStream_t st) {
+  const dim3 grid(s.N, s.B);
+  if (dtype == DT_BF16)
+    hipLaunchKernelGGL(verify_setup_kernel<bf16_t>, grid, dim3(256), 0, st, s, (const bf16_t*)E, x, rowtab);
+  else
+    hipLaunchKernelGGL(verify_setup_kernel<float>, grid, dim3(256), 0, st, s, (const float*)E, x, rowtab);
 }
 
 void launch_typical_stats(const float* logits, int rows, int V, int N, int b0, const int* n_b, const int* depth,
@@ -1039,17 +1079,12 @@ void launch_typical_stats(const float* logits, int rows, int V, int N, int b0, c
                      inv_T, seed, lse, H, sample);
 }
 
-void launch_accept(int, const StepState& s, hipStream_t st) {
-  hipLaunchKernelGGL(accept_kernel, dim3(s.B), dim3(64), 0, st, s);
-}
-
-void launch_compact(int dtype, const StepState& s, void* pool, int n_layers, int64_t layer_stride, hipStream_t st) {
+void launch_step_end(int dtype, const StepState& s, void* pool, int n_layers, int64_t layer_stride, hipStream_t st) {
+  const dim3 grid(2 * n_layers + s.K + 1, s.B);
   if (dtype == DT_BF16)
-    hipLaunchKernelGGL(compact_kernel<bf16_t>, dim3(n_layers, 2, s.B), dim3(256), 0, st, s, (bf16_t*)pool,
-                       layer_stride);
+    hipLaunchKernelGGL(step_end_kernel<bf16_t>, grid, dim3(256), 0, st, s, (bf16_t*)pool, n_layers, layer_stride);
   else
-    hipLaunchKernelGGL(compact_kernel<float>, dim3(n_layers, 2, s.B), dim3(256), 0, st, s, (float*)pool,
-                       layer_stride);
+    hipLaunchKernelGGL(step_end_kernel<float>, grid, dim3(256), 0, st, s, (float*)pool, n_layers, layer_stride);
 }
 
 void launch_kv_snapshot(int dtype, const StepState& s, const void* pool, int n_layers, int64_t layer_stride,
@@ -1070,13 +1105,6 @@ void launch_kv_check(int dtype, const StepState& s, const void* pool, int n_laye
   else
     hipLaunchKernelGGL(kv_check_kernel<float>, dim3(n_layers, 2, s.B), dim3(256), 0, st, s, (const float*)pool,
                        layer_stride, (const float*)side, counts);
-}
-
-void launch_advance(int dtype, const StepState& s, hipStream_t st) {
-  if (dtype == DT_BF16)
-    hipLaunchKernelGGL(advance_kernel<bf16_t>, dim3(s.B, s.K + 1), dim3(256), 0, st, s);
-  else
-    hipLaunchKernelGGL(advance_kernel<float>, dim3(s.B, s.K + 1), dim3(256), 0, st, s);
 }
 
 int draft_level_rows(const StepState& s, const DraftLevel& lv) {
@@ -1143,23 +1171,12 @@ void launch_prefill_finish(const StepState& s, const PrefillEnds& e, const int* 
 }
 
 // ---- phase timestamps ---------------------------------------------------------
-// One lane reads the GPU's constant-rate wall clock and stores it in the
-// current step's ring slot.  Kernels of a stream run one after another, so a
-// stamp launched between two phases records when the first phase's last
-// kernel has finished, and the four stamps of a step see the same counter.
-__global__ void stamp_kernel(unsigned long long* ring, unsigned int* counter, int idx, const int* n_b, int B) {
-  if (threadIdx.x != 0) return;
-  const unsigned int c = *counter;
-  unsigned long long* slot = ring + (size_t)(c % STAMP_RING) * STAMP_WORDS;
-  slot[idx] = __builtin_amdgcn_s_memrealtime();
-  if (idx == 0) {
-    unsigned long long sum = 0;
-    for (int b = 0; b < B; ++b) sum += (unsigned long long)n_b[b];
-    slot[4] = sum;
-  }
-  if (idx == 3) *counter = c + 1;
+// Stamp 3, the step's end, is a launch of its own: it runs when every kernel
+// of the step has finished.
+__global__ void stamp_kernel(StepState s) {
+  if (threadIdx.x == 0) stamp(s, 3);
 }
 
-void launch_stamp(unsigned long long* ring, unsigned int* counter, int idx, const int* n_b, int B, hipStream_t st) {
-  hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(64), 0, st, ring, counter, idx, n_b, B);
+void launch_stamp(const StepState& s, hipStream_t st) {
+  hipLaunchKernelGGL(stamp_kernel, dim3(1), dim3(64), 0, st, s);
 }
