@@ -1696,8 +1696,7 @@ chimera_status chimera_gemm_static(int32_t dtype, const void* x, const void* w, 
     char* base = static_scratch();
     // Rows of the last 16-row tile past M keep an earlier call's values; each
     // output row depends only on its own input row and rows >= M are not stored.
-    launch_tile_rows(dtype, x, M, K, base, mc / 16, st);
-    launch_repack(dtype, PACK_NATURAL, w, nullptr, nullptr, K, N, base + xb, 1, 64, st);
+    launch_stage_operands(dtype, x, M, K, base, mc / 16, w, N, base + xb, st);
     GemmShape s;
     s.X = base;
     s.x_mtiles = mc / 16;

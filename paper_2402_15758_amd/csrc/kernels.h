@@ -83,6 +83,9 @@ void launch_repack(int dtype, int kind, const void* src0, const void* src1, cons
                    void* dst, int H, int hd, hipStream_t st);
 // Row-major [M][K] -> tiled (test hook and one-off conversions).
 void launch_tile_rows(int dtype, const void* src, int M, int K, void* dst, int mtiles, hipStream_t st);
+// x [M][K] tiled and w [K][N] packed (natural order) in one launch.
+void launch_stage_operands(int dtype, const void* x, int M, int K, void* xd, int mtiles, const void* w, int N, void* wd,
+                           hipStream_t st);
 
 // ---- elementwise / norms ------------------------------------------------------
 void launch_embed(int dtype, const int* tokens, const void* E, float* x, int M, int d, int V, hipStream_t st);

@@ -527,6 +527,50 @@ __global__ void tile_rows_kernel(const T* __restrict__ src, int M, int K, T* __r
   copy_tiled<T>(dst, mtiles, r, c, src[tid]);
 }
 
+// Both operands of one product in a single launch (the static-scratch GEMM):
+// workgroups [0, nw) pack STAGE_KB k-blocks of a 64-column group of w each,
+// the others tile x.  Rows are read 16 bytes a lane, a k-block's 4 KiB in one
+// go, and the columns gathered from LDS: lanes that fetch a column each read
+// 2 bytes at a row's stride eight times over.
+constexpr int STAGE_KB = 4;
+template <typename T>
+__global__ __launch_bounds__(256) void stage_operands_kernel(const T* __restrict__ x, int M, int K, T* __restrict__ xd,
+                                                             int mtiles, const T* __restrict__ w, int N,
+                                                             T* __restrict__ wd, int nw) {
+  constexpr int VEC = ET<T>::VEC, KB = 4 * VEC, PPR = 64 / VEC;  // 16-byte pieces of a 64-column row
+  constexpr int PITCH = 64 + VEC;
+  __shared__ __attribute__((aligned(16))) T tile[STAGE_KB][KB * PITCH];
+  const int kblocks = K / KB, tid = threadIdx.x;
+  if ((int)blockIdx.x >= nw) {  // x: one 16-byte piece a thread, consecutive rows side by side in the tiles
+    const int64_t i = (int64_t)(blockIdx.x - nw) * 256 + tid;
+    if (i >= (int64_t)M * (K / VEC)) return;
+    const int r = (int)(i % M), q = (int)(i / M);
+    st16(xd + tiled_index<T>(mtiles, r, q * VEC), ld16(x + (int64_t)r * K + q * VEC));
+    return;
+  }
+  const int kgroups = (kblocks + STAGE_KB - 1) / STAGE_KB;
+  const int grp = blockIdx.x / kgroups, kb0 = blockIdx.x % kgroups * STAGE_KB, n = min(STAGE_KB, kblocks - kb0);
+  const int row = tid / PPR, piece = tid % PPR;  // KB rows x PPR pieces = 256
+  int4 v[STAGE_KB];
+#pragma unroll
+  for (int k = 0; k < STAGE_KB; ++k)
+    if (k < n) v[k] = ld16(w + ((int64_t)(kb0 + k) * KB + row) * N + grp * 64 + piece * VEC);
+#pragma unroll
+  for (int k = 0; k < STAGE_KB; ++k)
+    if (k < n) st16(&tile[k][row * PITCH + piece * VEC], v[k]);
+  __syncthreads();
+  const int lane = tid & 63, col = 16 * (tid >> 6) + (lane & 15), k0 = (lane >> 4) * VEC;
+#pragma unroll
+  for (int k = 0; k < STAGE_KB; ++k) {
+    if (k >= n) break;
+    int4 o;
+    T* e = reinterpret_cast<T*>(&o);
+#pragma unroll
+    for (int j = 0; j < VEC; ++j) e[j] = tile[k][(k0 + j) * PITCH + col];
+    st16(wd + (((int64_t)grp * kblocks + kb0 + k) * 256 + tid) * VEC, o);
+  }
+}
+
 }  // namespace
 
 void launch_tile_rows(int dtype, const void* src, int M, int K, void* dst, int mtiles, hipStream_t st) {
@@ -536,6 +580,24 @@ void launch_tile_rows(int dtype, const void* src, int M, int K, void* dst, int m
     hipLaunchKernelGGL(tile_rows_kernel<bf16_t>, grid, dim3(256), 0, st, (const bf16_t*)src, M, K, (bf16_t*)dst, mtiles);
   else
     hipLaunchKernelGGL(tile_rows_kernel<float>, grid, dim3(256), 0, st, (const float*)src, M, K, (float*)dst, mtiles);
+}
+
+void launch_stage_operands(int dtype, const void* x, int M, int K, void* xd, int mtiles, const void* w, int N, void* wd,
+                           hipStream_t st) {
+  if (((uintptr_t)x | (uintptr_t)w) & 15) {  // the caller's matrices may start anywhere; their rows are whole pieces
+    launch_tile_rows(dtype, x, M, K, xd, mtiles, st);
+    launch_repack(dtype, PACK_NATURAL, w, nullptr, nullptr, K, N, wd, 1, 64, st);
+    return;
+  }
+  const int VEC = dtype == DT_BF16 ? 8 : 4, kblocks = K / (4 * VEC);
+  const int nw = N / 64 * ((kblocks + STAGE_KB - 1) / STAGE_KB);
+  const int nx = (int)(((int64_t)M * (K / VEC) + 255) / 256);
+  if (dtype == DT_BF16)
+    hipLaunchKernelGGL(stage_operands_kernel<bf16_t>, dim3(nw + nx), dim3(256), 0, st, (const bf16_t*)x, M, K,
+                       (bf16_t*)xd, mtiles, (const bf16_t*)w, N, (bf16_t*)wd, nw);
+  else
+    hipLaunchKernelGGL(stage_operands_kernel<float>, dim3(nw + nx), dim3(256), 0, st, (const float*)x, M, K, (float*)xd,
+                       mtiles, (const float*)w, N, (float*)wd, nw);
 }
 
 int gemm_pick_splits(int n_cols, int K, int dtype) {

@@ -51,9 +51,11 @@ sys.path.insert(0, ROOT)
 OUT_DIR = os.environ.get("PROFILES_DIR", os.path.join(ROOT, "profiles"))
 HBM_PEAK = 8.0e12
 BF16_PEAK = 2.5e15
-GEMM_SOURCES = ["paper_2402_15758_amd/csrc/kernels_gemm.hip", "paper_2402_15758_amd/csrc/common.h",
+GEMM_SOURCES = ["paper_2402_15758_amd/csrc/kernels_gemm.hip", "paper_2402_15758_amd/csrc/kernels_gemm_wide.hip",
+                "paper_2402_15758_amd/csrc/gemm_epilogue.h", "paper_2402_15758_amd/csrc/common.h",
                 "paper_2402_15758_amd/csrc/kernels.h", "paper_2402_15758_amd/build.py"]
 GEMM_RE = re.compile(r"gemm_kernel<[^,]+, (\d+), (\d+)")
+WIDE_RE = re.compile(r"gemm_wide_kernel<[^,]+, \d+, (\d+), \d+, (\d+)")
 
 
 def short(name):
@@ -62,8 +64,16 @@ def short(name):
 
 
 def gemm_mb(name):
+    """16-row tiles of a GEMM launch's row block (0: not a GEMM)."""
     m = GEMM_RE.search(name)
-    return int(m.group(1)) if m else 0
+    if m:
+        return int(m.group(1))
+    m = WIDE_RE.search(name)
+    return int(m.group(1)) * int(m.group(2)) if m else 0
+
+
+def is_gemm(name):
+    return gemm_mb(name) > 0
 
 
 def sources_sha():
@@ -87,12 +97,27 @@ def verify_roles(cfg, M):
     return [(r, n, k, n * k * es + M * k * es + M * n * 4) for r, n, k in out]
 
 
-def step_groups(rows, is_stamp, name_of):
-    """Indices of the stamp kernels, grouped four per decode step."""
-    st = [i for i, r in enumerate(rows) if is_stamp(r)]
-    if len(st) % 4:
-        raise SystemExit(f"{len(st)} stamp kernels: not a whole number of steps")
-    return [st[i:i + 4] for i in range(0, len(st), 4)]
+def step_marks(names):
+    """Indices of each decode step's four phase marks: step start, verify
+    start, verify end, step end.  The first three are the kernels that take
+    the phase stamps as they start (the first draft rows, or the verify setup
+    where there is no draft; the verify setup; the step end), the last the
+    stamp kernel.  Traces whose steps launch four stamp kernels use those."""
+    st = [i for i, n in enumerate(names) if "stamp_kernel" in n]
+    if not any("verify_setup_kernel" in n for n in names):
+        if len(st) % 4:
+            raise SystemExit(f"{len(st)} stamp kernels: not a whole number of steps")
+        return [st[i:i + 4] for i in range(0, len(st), 4)]
+    out, prev = [], -1
+    for e in st:
+        setup = [i for i in range(prev + 1, e) if "verify_setup_kernel" in names[i]]
+        end = [i for i in range(prev + 1, e) if "step_end_kernel" in names[i]]
+        if len(setup) != 1 or len(end) != 1:
+            raise SystemExit("a step without its verify setup or step end kernel")
+        draft = [i for i in range(prev + 1, setup[0]) if "draft_rows_kernel" in names[i]]
+        out.append([draft[0] if draft else setup[0], setup[0], end[0], e])
+        prev = e
+    return out
 
 
 # --------------------------------------------------------------------------
@@ -106,7 +131,10 @@ def trace(d, wl_name, warmup, steps, cmd):
     rows = list(csv.DictReader(open(os.path.join(d, "run_kernel_trace.csv"))))
     rows.sort(key=lambda r: int(r["Start_Timestamp"]))
     t = lambda r, k: int(r[k])
-    groups = step_groups(rows, lambda r: "stamp_kernel" in r["Kernel_Name"], None)
+    groups = step_marks([r["Kernel_Name"] for r in rows])
+    # a phase runs from its mark's start where the mark works for it, from the
+    # end of the stamp kernel otherwise
+    since = lambda r: t(r, "End_Timestamp" if "stamp_kernel" in r["Kernel_Name"] else "Start_Timestamp")
     spec = [g for g in groups if any(gemm_mb(rows[i]["Kernel_Name"]) > 1 for i in range(g[1] + 1, g[2]))]
     if len(spec) < warmup + 3 * steps:
         raise SystemExit(f"{len(spec)} speculative steps in the trace, expected at least {warmup + 3 * steps}")
@@ -119,9 +147,9 @@ def trace(d, wl_name, warmup, steps, cmd):
            f"{cfg.head_dim}, F {cfg.d_ffn}, vocab {cfg.vocab}, {cfg.dtype}; batch {B}, tree of {N} nodes "
            f"({M} verify rows). Made by\n\n```\n{cmd}\npython profile_summary.py trace <DIR> {wl_name} "
            f"{warmup} {steps} \"<command>\"\n```\n\n"
-           "Steps are delimited by the library's wall-clock stamp kernels (draft start, verify start, "
-           "verify end, step end); spans below run from the end of one stamp kernel to the start of the "
-           "next, so they include the launch gaps inside the span.\n\n"
+           "Steps are delimited by the kernels that take the library's wall-clock stamps (draft start, "
+           "verify start, verify end, step end); spans below run from one to the next, so they include the "
+           "launch gaps inside the span.\n\n"
            "| pass | steps | step us | draft us | verify us | tail us | verify GEMM launches/step | "
            "verify GEMM avg us | verify GEMM us/step |\n|---|---:|---:|---:|---:|---:|---:|---:|---:|\n"]
     role_us = {}
@@ -131,9 +159,9 @@ def trace(d, wl_name, warmup, steps, cmd):
         per_role = collections.defaultdict(list)
         for g in sel:
             for p in range(3):
-                ph[p].append((t(rows[g[p + 1]], "Start_Timestamp") - t(rows[g[p]], "End_Timestamp")) / 1e3)
-            ph[3].append((t(rows[g[3]], "Start_Timestamp") - t(rows[g[0]], "End_Timestamp")) / 1e3)
-            launches = [rows[i] for i in range(g[1] + 1, g[2]) if "gemm_kernel" in rows[i]["Kernel_Name"]]
+                ph[p].append((t(rows[g[p + 1]], "Start_Timestamp") - since(rows[g[p]])) / 1e3)
+            ph[3].append((t(rows[g[3]], "Start_Timestamp") - since(rows[g[0]])) / 1e3)
+            launches = [rows[i] for i in range(g[1] + 1, g[2]) if is_gemm(rows[i]["Kernel_Name"])]
             if len(launches) != len(roles):
                 raise SystemExit(f"{len(launches)} GEMM launches in a verify span, expected {len(roles)}")
             for (role, _, _, _), r in zip(roles, launches):
@@ -176,7 +204,7 @@ def trace(d, wl_name, warmup, steps, cmd):
     agg = collections.defaultdict(lambda: [0.0, 0])
     busy = 0.0
     for g in sel:
-        for i in range(g[0] + 1, g[3]):
+        for i in range(g[0], g[3]):
             r = rows[i]
             if "stamp_kernel" in r["Kernel_Name"]:
                 continue
@@ -217,10 +245,9 @@ def load_counters(path):
 
 def verify_gemms(ds):
     """Per speculative step: the verify GEMM dispatches, in launch order."""
-    st = [i for i, e in enumerate(ds) if "stamp_kernel" in e["name"]]
     out = []
-    for g in (st[i:i + 4] for i in range(0, len(st) - 3, 4)):
-        launches = [ds[i] for i in range(g[1] + 1, g[2]) if "gemm_kernel" in ds[i]["name"]]
+    for g in step_marks([e["name"] for e in ds]):
+        launches = [ds[i] for i in range(g[1] + 1, g[2]) if is_gemm(ds[i]["name"])]
         if any(gemm_mb(e["name"]) > 1 for e in launches):
             out.append(launches)
     return out
@@ -334,9 +361,8 @@ def attn(d, wl_name, cmd_sq, cmd_f=None, cmd_w=None):
     sample, their HBM bytes scaled by the sample's 1 GiB copies."""
 
     def verify_attn(ds):
-        st = [i for i, e in enumerate(ds) if "stamp_kernel" in e["name"]]
         per = {k: [] for k in ATTN_KERNELS}
-        for g in (st[i:i + 4] for i in range(0, len(st) - 3, 4)):
+        for g in step_marks([e["name"] for e in ds]):
             for i in range(g[1] + 1, g[2]):
                 for k in ATTN_KERNELS:
                     if k in ds[i]["name"]:

@@ -63,6 +63,29 @@ def test_rows_keep_their_bits_in_launches_of_a_few_rows(dtype, N, K, Ms):
         assert np.array_equal(y.view(np.uint32), ref[:M].view(np.uint32)), f"M={M}"
 
 
+# the static-scratch product stages its operands 16 bytes at a time where both
+# start on a 16-byte boundary, and element by element where one does not; k-block
+# counts around the four a workgroup packs, rows around the 16-row tile
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 1, 64, 32), ("bf16", 17, 192, 160), ("bf16", 130, 64, 128),
+                                         ("f32", 5, 128, 16), ("f32", 16, 64, 80)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_static_gemm_stages_any_alignment(dtype, M, N, K, shift):
+    print(f"static gemm {dtype} M={M} N={N} K={K} shift={shift}", flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dt = B.CHIMERA_F32 if dtype == "f32" else B.CHIMERA_BF16
+    g = torch.Generator().manual_seed(M + N + K)
+    x = torch.randn((M, K), generator=g).to(tdt)
+    w = torch.randn((K, N), generator=g).to(tdt)
+    dx = torch.zeros(M * K + shift, dtype=tdt, device="cuda")[shift:].copy_(x.view(-1))
+    dw = torch.zeros(K * N + shift, dtype=tdt, device="cuda")[shift:].copy_(w.view(-1))
+    y = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    B.chimera_gemm_static(dt, dx.data_ptr(), dw.data_ptr(), M, N, K, y.data_ptr(),
+                          torch.cuda.current_stream().cuda_stream)
+    bits = (lambda t: t.numpy()) if dtype == "f32" else (lambda t: t.view(torch.int16).numpy().view(np.uint16))
+    want = _gemm(dt, bits(x).copy(), bits(w).copy())
+    assert np.array_equal(y.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
 def _states(sess):
     """What two steps after the prefill show of every sequence."""
     out = [[] for _ in range(sess.batch)]
