@@ -657,7 +657,8 @@ __global__ __launch_bounds__(256) void enc_attn_partial(const EncAttnArgs a) {
   }
 }
 
-template <typename T, int HD>
+// CB: block partials requested per round trip.
+template <typename T, int HD, int CB>
 __global__ void enc_attn_combine(const EncAttnArgs a) {
   constexpr int DPL = HD / 64;
   const int h = blockIdx.x, row = blockIdx.y, lane = threadIdx.x;
@@ -668,7 +669,6 @@ __global__ void enc_attn_combine(const EncAttnArgs a) {
 #pragma unroll
   for (int e = 0; e < DPL; ++e) o[e] = 0.f;
   // block partials are requested CB at a time, then folded in block order
-  constexpr int CB = 8;
   for (int b0 = 0; b0 < used; b0 += CB) {
     float bm[CB], bl[CB], bo[CB][DPL];
 #pragma unroll
@@ -703,7 +703,13 @@ __global__ void enc_attn_combine(const EncAttnArgs a) {
 template <typename T, int HD>
 void enc_attn_go(const EncAttnArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((enc_attn_partial<T, HD>), dim3(a.nblk, a.H, a.B * a.R), dim3(256), 0, st, a);
-  hipLaunchKernelGGL((enc_attn_combine<T, HD>), dim3(a.H, a.B * a.R), dim3(64), 0, st, a);
+  // The fold is a chain, its loads need not be: memories of more than 12 blocks
+  // (1500 positions) take 24 partials a round trip (33 blocks at a 4096-token
+  // context: 14.6 -> 12.1 us; batch 8: 9.5 -> 7.7), shorter ones 8.
+  if (a.nblk > 12)
+    hipLaunchKernelGGL((enc_attn_combine<T, HD, 24>), dim3(a.H, a.B * a.R), dim3(64), 0, st, a);
+  else
+    hipLaunchKernelGGL((enc_attn_combine<T, HD, 8>), dim3(a.H, a.B * a.R), dim3(64), 0, st, a);
 }
 
 }  // namespace
