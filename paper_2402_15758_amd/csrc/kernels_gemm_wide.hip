@@ -42,10 +42,13 @@ struct Int {
   static constexpr int value = N;
 };
 
-// s_waitcnt vmcnt(N) alone (lgkmcnt and expcnt unconstrained).
+// s_waitcnt vmcnt(N) lgkmcnt(0): all but the N youngest loads into LDS have
+// landed, and every LDS read issued so far has its data (an MFMA may be
+// scheduled past the barrier that follows; the read that feeds it must not
+// still be in flight when the barrier lets its buffer be refilled).
 template <int N>
 __device__ __forceinline__ void wait_vm() {
-  __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
 }
 __device__ __forceinline__ void wg_barrier() {
   asm volatile("" ::: "memory");
