@@ -62,6 +62,14 @@ struct GemmShape {
 // consumers of split-K partials load them all at once).
 constexpr int GEMM_MAX_SPLITS = 8;
 int gemm_pick_splits(int n_cols, int K, int dtype);
+// How the streaming kernel deals a launch out: row_blocks x runs workgroups a
+// slice, each with row_tiles 16-row tiles and a run of column blocks (the first
+// long_runs runs `run` blocks long, the others run - 1); mapped: the row blocks
+// of a run stay on one die.
+struct StreamPlan {
+  int row_tiles, row_blocks, runs, run, long_runs, mapped;
+};
+StreamPlan gemm_stream_plan(int M, int nbc, int splits, int x_mtiles);
 // Partials [parts][M][N] that an EPI_PARTIAL launch writes: its slices, or 1
 // where a launch of many rows adds them (in slice order) itself.
 int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles);

@@ -389,8 +389,8 @@ void go_slices(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t 
 }  // namespace
 
 bool gemm_wide_takes(int dtype, int M, int K, int x_mtiles) {
-  // up to 128 rows the row-split-free kernel is faster (QKV at 128 rows 33 us
-  // against 37 us); its K offsets are 32-bit
+  // up to 128 rows the streaming kernel is faster (QKV at 128 rows 33 us
+  // against 37 us); this kernel's K offsets are 32-bit
   return dtype == DT_BF16 && M > 128 && (int64_t)K * 16 * x_mtiles * 2 < (int64_t)1 << 32 && K < 1 << 24;
 }
 
