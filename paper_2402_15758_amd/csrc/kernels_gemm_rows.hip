@@ -121,13 +121,29 @@ void go_kind(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea
 }  // namespace
 
 bool gemm_rows_takes(int dtype, int M, int nbc, int K, int splits, int kind) {
-  // One workgroup per CU streams its block at the same rate as all others, so
-  // a last round that is mostly empty costs more than the finishing launch
-  // (320 blocks of K = 15360: 33 us against 28 + 4).
+  if (splits <= 1 || splits > GEMM_MAX_SPLITS || M > 16) return false;
+  if (kind != EPI_F32 && kind != EPI_SILU && kind != EPI_ZIN) return false;
+  const int es = dtype == DT_BF16 ? 2 : 4;
+  const int64_t rows = (int64_t)M * K * es, weights = (int64_t)16 * K * es;
+  if (rows > MAX_LDS_X) return false;
+  if (nbc <= 256) {
+    // One round.  With most CUs busy the weights stream at the card's rate
+    // either way (256 blocks, K = 4096 bf16, one row: 9.0 us against 10.2 with
+    // the slices side by side and the finishing launch).  With fewer blocks one
+    // CU takes in what `splits` of them would: worth the launch saved (1.5 to 4
+    // us, more the more columns it has) while a block is short.  Against the
+    // split launches, us, one row, bf16: 64 columns K = 2048 3.4 / 4.2, K = 4096
+    // 6.3 / 4.6, K = 32768 24 / 8.4; 2560 columns K = 3072 6.0 / 7.4, K = 6144
+    // 10.9 / 9.9; fp32 (four MFMAs a k-block): 512 columns K = 1024 4.4 / 5.0,
+    // K = 2048 7.9 / 5.3.
+    return nbc >= 224 || weights + rows / 2 <= (dtype == DT_BF16 ? 104 << 10 : 80 << 10) + 64 * es * nbc;
+  }
+  // More rounds: the last may not be mostly empty (320 blocks of K = 15360: 33
+  // us against 28 + 4), and two workgroups have to fit a CU's LDS for one round
+  // to start under the other (480 blocks, 16 rows of bf16: K = 1280 7.3 / 8.6
+  // us, K = 1536 10.4 / 9.2).
   const int rounds = (nbc + 255) / 256;
-  return (rounds == 1 || 10 * (rounds * 256 - nbc) <= nbc) && splits > 1 && splits <= GEMM_MAX_SPLITS && M <= 16 &&
-         (kind == EPI_F32 || kind == EPI_SILU || kind == EPI_ZIN) &&
-         (int64_t)M * K * (dtype == DT_BF16 ? 2 : 4) <= MAX_LDS_X;
+  return 10 * (rounds * 256 - nbc) <= nbc && rows <= 46 << 10;
 }
 
 void launch_gemm_rows(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {

@@ -42,3 +42,25 @@ def test_a_plan_covers_every_row_and_column_block_once(M):
             assert p.long_runs * p.run + (p.runs - p.long_runs) * (p.run - 1) == nbc
             assert 1 <= p.long_runs <= p.runs and 1 <= p.run <= (6 if p.row_tiles == 8 else 8)
             assert 16 * p.row_tiles * (p.row_blocks - 1) < M <= 16 * p.row_tiles * p.row_blocks
+
+
+F32, SILU, SWIGLU, QKV, PARTIAL, ZIN = 0, 2, 3, 4, 5, 6
+
+
+def splits_of(bf16, cols, K):
+    return _fn("_Z16gemm_pick_splitsiii", ctypes.c_int)(cols, K, bf16)
+
+
+# Launches of a few rows whose slices meet in one workgroup per column block,
+# and those that run their slices side by side on more CUs (measured faster).
+@pytest.mark.parametrize("bf16,M,cols,K,one", [
+    (1, 1, 64, 2048, True), (1, 1, 64, 4096, False), (1, 1, 64, 32768, False), (1, 4, 1024, 8192, False),
+    (1, 1, 2048, 4096, False), (1, 16, 1024, 2048, True), (1, 1, 2560, 3072, True), (1, 1, 4096, 16384, True),
+    (1, 1, 4096, 11008, True), (1, 16, 7680, 1280, True), (1, 16, 7680, 1536, False), (1, 1, 5120, 15360, False),
+    (0, 5, 1024, 1024, True), (0, 1, 64, 2048, False), (0, 1, 1024, 4096, False), (0, 8, 256, 768, True),
+])
+def test_few_row_launches_where_one_workgroup_a_block_is_faster(bf16, M, cols, K, one):
+    takes = _fn("_Z15gemm_rows_takesiiiiii", ctypes.c_bool)
+    for kind in (F32, SILU, ZIN):
+        assert takes(bf16, M, cols // 16, K, splits_of(bf16, cols, K), kind) == one
+    assert not takes(bf16, M, cols // 16, K, splits_of(bf16, cols, K), PARTIAL)

@@ -46,6 +46,7 @@ def test_rows_keep_their_bits_in_wide_launches(N, K):
 @pytest.mark.parametrize("dtype,N,K,Ms", [
     ("bf16", 192, 1024, (1, 16)), ("bf16", 64, 4096, (1, 3, 15)), ("bf16", 4096, 8192, (1, 7, 8)),
     ("bf16", 1088, 5504, (2, 11)), ("f32", 256, 768, (1, 7, 16)), ("f32", 64, 2048, (1, 15, 16)),
+    ("bf16", 3584, 4096, (1, 3, 15)), ("f32", 3584, 2048, (1, 15)),  # eight slices in one workgroup
 ])
 def test_rows_keep_their_bits_in_launches_of_a_few_rows(dtype, N, K, Ms):
     print(f"few rows {dtype} N={N} K={K}", flush=True)
