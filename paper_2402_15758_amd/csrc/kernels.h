@@ -80,8 +80,11 @@ void launch_gemm_rows(int dtype, const GemmShape& s, const GemmEpi& e, hipStream
 // Launches of many rows (kernels_gemm_wide.hip, bf16): the same sums on 2-D
 // output tiles.  sums_slices: the launch applies its epilogue to the whole
 // sum; otherwise a split launch writes one partial per slice.
-bool gemm_wide_takes(int dtype, int M, int K, int x_mtiles);
+bool gemm_wide_takes(int dtype, int M, int nbc, int K, int splits, int x_mtiles);
 bool gemm_wide_sums_slices(int M, int nbc, int kind);
+// Output tile of such a launch, kps k-blocks a slice: 0 256x192, 1 256x128, 2
+// 256x96, 3 128x128, 4 128x96.
+int gemm_wide_tile(int M, int nbc, int kps, int splits);
 void launch_gemm_wide(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb);
 // ev_start / ev_stop (optional): recorded by the dispatch of the GEMM's
 // first and last kernel (hipExtLaunchKernel), i.e. the kernel execution span.

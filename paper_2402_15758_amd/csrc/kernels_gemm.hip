@@ -613,8 +613,9 @@ int gemm_pick_splits(int n_cols, int K, int dtype) {
 }
 
 int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles) {
-  if (gemm_wide_takes(dtype, M, K, x_mtiles) && gemm_wide_sums_slices(M, n_cols / 16, EPI_PARTIAL)) return 1;
-  return gemm_pick_splits(n_cols, K, dtype);
+  const int splits = gemm_pick_splits(n_cols, K, dtype), nbc = n_cols / 16;
+  if (gemm_wide_takes(dtype, M, nbc, K, splits, x_mtiles) && gemm_wide_sums_slices(M, nbc, EPI_PARTIAL)) return 1;
+  return splits;
 }
 
 void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start,
@@ -624,7 +625,7 @@ void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st
     launch_gemm_rows(dtype, s, e, st, ev_start, ev_stop);
     return;
   }
-  if (gemm_wide_takes(dtype, s.M, s.K, s.x_mtiles)) {
+  if (gemm_wide_takes(dtype, s.M, gemm_blocks(s), s.K, s.splits, s.x_mtiles)) {
     const bool finish = s.splits > 1 && e.kind != EPI_PARTIAL && !gemm_wide_sums_slices(s.M, gemm_blocks(s), e.kind);
     if (finish) {
       GemmEpi p = e;

@@ -347,6 +347,37 @@ Tile pick_tile(int M, int nbc, int kps) {
 constexpr int SLICES_IN_WG_TILES = 192;
 bool slices_in_wg(int M, int nbc) { return tiles_of(BIG, M, nbc) >= SLICES_IN_WG_TILES; }
 
+}  // namespace
+
+int gemm_wide_tile(int M, int nbc, int kps, int splits) {
+  if (splits == 1) return pick_tile(M, nbc, kps);
+  return slices_in_wg(M, nbc) || tiles_of(BIG, M, nbc) * splits >= 256 ? BIG : SQ;
+}
+
+namespace {
+
+// Time of a launch in us, from what a CU takes in (1 KiB tiles, 16 rows or
+// columns by a k-block) and its output tiles, in rounds of 256 workgroups.
+// Fitted to 991 launches of 129 to 2048 rows, 64 to 32000 columns and K from
+// 256 to 16384 on both kernels: a CU takes in about 70 GB/s, a streaming
+// workgroup reduces and stores an output tile in 0.1 us (its four waves meet in
+// LDS), one of this kernel's (eight waves, no reduction) in 0.0125 us.  Picked
+// by it no launch is more than 4% slower than on the streaming kernel, 13 are
+// on this one.
+double launch_us(double fixed, int wgs, int kblocks, int row_tiles, int blocks, double in_us, double out_us) {
+  return fixed + (wgs + 255) / 256 * ((double)kblocks * (row_tiles + blocks) * in_us + row_tiles * blocks * out_us);
+}
+double stream_us(int M, int nbc, int kps, int splits, int x_mtiles) {
+  const StreamPlan p = gemm_stream_plan(M, nbc, splits, x_mtiles);
+  return launch_us(2.0, p.row_blocks * p.runs * splits, kps, p.row_tiles, p.run, 14.0 / 1024, 0.1);
+}
+double wide_us(int M, int nbc, int kps, int splits) {
+  const bool sl = splits > 1 && slices_in_wg(M, nbc);
+  const Tile t = (Tile)gemm_wide_tile(M, nbc, kps, splits);
+  return launch_us(3.5, tiles_of(t, M, nbc) * (sl ? 1 : splits), sl ? kps * splits : kps, TILE_ROWS[t] / 16, TILE_BLKS[t],
+                   15.0 / 1024, 0.0125);
+}
+
 template <typename T, int KIND, int WM, int WN, int MT, int CB, bool SL>
 void go(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
   constexpr int NS = 4;
@@ -372,7 +403,7 @@ void go(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hip
 
 template <int KIND>
 void go_unsplit(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
-  switch (pick_tile(s.M, s.nb_count ? s.nb_count : s.N / 16, s.K / (4 * ET<bf16_t>::VEC) / s.splits)) {
+  switch (gemm_wide_tile(s.M, s.nb_count ? s.nb_count : s.N / 16, s.K / (4 * ET<bf16_t>::VEC), 1)) {
     case XL: go<bf16_t, KIND, 4, 2, 4, 6, false>(s, e, st, ea, eb); break;
     case BIG: go<bf16_t, KIND, 4, 2, 4, 4, false>(s, e, st, ea, eb); break;
     case MED: go<bf16_t, KIND, 4, 2, 4, 3, false>(s, e, st, ea, eb); break;
@@ -388,10 +419,16 @@ void go_slices(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t 
 
 }  // namespace
 
-bool gemm_wide_takes(int dtype, int M, int K, int x_mtiles) {
+bool gemm_wide_takes(int dtype, int M, int nbc, int K, int splits, int x_mtiles) {
   // up to 128 rows the streaming kernel is faster (QKV at 128 rows 33 us
   // against 37 us); this kernel's K offsets are 32-bit
-  return dtype == DT_BF16 && M > 128 && (int64_t)K * 16 * x_mtiles * 2 < (int64_t)1 << 32 && K < 1 << 24;
+  if (dtype != DT_BF16 || M <= 128 || (int64_t)K * 16 * x_mtiles * 2 >= (int64_t)1 << 32 || K >= 1 << 24) return false;
+  // Matrices too small for its tiles to reach most CUs, and those whose
+  // columns the streaming kernel deals in shorter runs, stay on that one, us:
+  // 256 rows 768 x 256 3.8 / 5.8, 1024 x 4096 14.7 / 15.6, 8192 x 4096 30.6 /
+  // 39.4, 5120 x 13824 68 / 77; 512 rows 2048 x 256 5.5 / 6.6.
+  const int kps = K / 32 / splits;
+  return wide_us(M, nbc, kps, splits) <= stream_us(M, nbc, kps, splits, x_mtiles);
 }
 
 bool gemm_wide_sums_slices(int M, int nbc, int kind) {
@@ -405,7 +442,7 @@ void launch_gemm_wide(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipE
     else if (e.kind == EPI_F32) go_slices<EPI_F32>(s, e, st, ea, eb);
     else go_slices<EPI_SILU>(s, e, st, ea, eb);
   } else if (e.kind == EPI_PARTIAL) {
-    if (tiles_of(BIG, s.M, nbc) * s.splits >= 256)
+    if (gemm_wide_tile(s.M, nbc, s.K / (4 * ET<bf16_t>::VEC) / s.splits, s.splits) == BIG)
       go<bf16_t, EPI_PARTIAL, 4, 2, 4, 4, false>(s, e, st, ea, eb);
     else
       go<bf16_t, EPI_PARTIAL, 4, 2, 2, 4, false>(s, e, st, ea, eb);

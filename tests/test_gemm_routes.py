@@ -1,25 +1,9 @@
 """Which kernel a GEMM launch runs on and how it is dealt out: the host-side
 rules of kernels.h, called in the built library (no GPU)."""
-import ctypes
-
 import pytest
 
+from gemm_launch import (EPI_F32, EPI_PARTIAL, EPI_SILU, EPI_ZIN, rows_takes, stream_plan, wide_takes)
 from paper_2402_15758_amd import binding as B
-
-
-class StreamPlan(ctypes.Structure):
-    _fields_ = [(n, ctypes.c_int) for n in ("row_tiles", "row_blocks", "runs", "run", "long_runs", "mapped")]
-
-
-def _fn(name, restype):
-    f = B.lib()[name]
-    f.restype = restype
-    return f
-
-
-def stream_plan(M, nbc, splits):
-    mcap = next((c for c in (16, 32, 64) if M <= c), -(-M // 128) * 128)
-    return _fn("_Z16gemm_stream_planiiii", StreamPlan)(M, nbc, splits, mcap // 16)
 
 
 # bf16 launches of two 64-row blocks: 65 to 128 rows of matrices dealt in runs
@@ -44,13 +28,6 @@ def test_a_plan_covers_every_row_and_column_block_once(M):
             assert 16 * p.row_tiles * (p.row_blocks - 1) < M <= 16 * p.row_tiles * p.row_blocks
 
 
-F32, SILU, SWIGLU, QKV, PARTIAL, ZIN = 0, 2, 3, 4, 5, 6
-
-
-def splits_of(bf16, cols, K):
-    return _fn("_Z16gemm_pick_splitsiii", ctypes.c_int)(cols, K, bf16)
-
-
 # Launches of a few rows whose slices meet in one workgroup per column block,
 # and those that run their slices side by side on more CUs (measured faster).
 @pytest.mark.parametrize("bf16,M,cols,K,one", [
@@ -60,7 +37,20 @@ def splits_of(bf16, cols, K):
     (0, 5, 1024, 1024, True), (0, 1, 64, 2048, False), (0, 1, 1024, 4096, False), (0, 8, 256, 768, True),
 ])
 def test_few_row_launches_where_one_workgroup_a_block_is_faster(bf16, M, cols, K, one):
-    takes = _fn("_Z15gemm_rows_takesiiiiii", ctypes.c_bool)
-    for kind in (F32, SILU, ZIN):
-        assert takes(bf16, M, cols // 16, K, splits_of(bf16, cols, K), kind) == one
-    assert not takes(bf16, M, cols // 16, K, splits_of(bf16, cols, K), PARTIAL)
+    for kind in (EPI_F32, EPI_SILU, EPI_ZIN):
+        assert rows_takes(bf16, M, cols, K, kind) == one
+    assert not rows_takes(bf16, M, cols, K, EPI_PARTIAL)
+
+
+# Launches of more than 128 bf16 rows: the faster of the two kernels (both
+# timed), 7B and 13B projections and small or narrow matrices.
+@pytest.mark.parametrize("M,cols,K,tiled", [
+    (256, 768, 256, False), (512, 2048, 256, False), (2048, 256, 256, False), (256, 64, 16384, False),
+    (256, 4096, 256, False), (256, 8192, 4096, False), (129, 8192, 8192, False), (256, 5120, 13824, False),
+    (256, 4096, 4096, True), (256, 4096, 11008, True), (256, 22016, 4096, True), (129, 32000, 4096, True),
+    (512, 8192, 4096, True), (512, 12288, 4096, True), (2048, 1024, 4096, True), (2048, 4096, 512, True),
+    (128, 32000, 4096, False),
+])
+def test_wide_launches_run_on_the_faster_kernel(M, cols, K, tiled):
+    assert wide_takes(1, M, cols, K) == tiled
+    assert not wide_takes(0, M, cols, K)

@@ -1,14 +1,16 @@
 """Launches of many rows: the 2-D tiled GEMM and the packed prefill chunks.
 
 A row's arithmetic does not depend on how many rows a launch carries, so every
-comparison here is exact: a product of 129 to 256 rows (the tiled kernel)
-against the same rows in launches of at most 128 (the streaming kernel), and
-prompts prefilled together, in chunks of up to 2048 rows, against each prompt
-prefilled alone."""
+comparison here is exact: a product of more than 128 rows, by whichever kernel
+its shape takes and by the tiled kernel with each of its output tiles, against
+the same rows in launches of at most 128 (the streaming kernel), and prompts
+prefilled together, in chunks of up to 2048 rows, against each prompt prefilled
+alone."""
 import numpy as np
 import pytest
 import torch  # before the library: both then share one HIP runtime
 
+import gemm_launch as G
 import synth
 from paper_2402_15758_amd import Session
 from paper_2402_15758_amd import binding as B
@@ -25,7 +27,8 @@ def _gemm(dtype, x, w):
 
 # N, K: one 16-column group up to unsplit width; K below one k-block per wave,
 # ragged classes (K / 32 not a multiple of 16), split K with even and odd slices;
-# 33024 columns: the widest tile
+# the tiled kernel takes (8256, 160) and (33024, 512), the streaming kernel, in
+# several row blocks, the others
 @pytest.mark.parametrize("N,K", [(64, 32), (64, 96), (192, 544), (320, 1024), (2048, 2048), (1088, 5504), (8256, 160),
                                  (33024, 512)])
 def test_rows_keep_their_bits_in_wide_launches(N, K):
@@ -38,6 +41,94 @@ def test_rows_keep_their_bits_in_wide_launches(N, K):
     for M in (129, 200, 256):
         y = _gemm(B.CHIMERA_BF16, x[:M].copy(), w)
         assert np.array_equal(y.view(np.uint32), ref[:M].view(np.uint32)), f"M={M}"
+
+
+def _tiled(x, mtiles):
+    """x [rows][K] bf16 in fragment order, `mtiles` 16-row tiles."""
+    rows, K = x.shape
+    t = torch.zeros((mtiles * 16, K), dtype=x.dtype, device=x.device)
+    t[:rows] = x
+    return t.view(mtiles, 16, K // 32, 4, 8).permute(2, 0, 3, 1, 4).contiguous()
+
+
+def _untiled(t, mtiles, cols, rows):
+    return t.view(cols // 32, mtiles, 4, 16, 8).permute(1, 3, 0, 2, 4).reshape(mtiles * 16, cols)[:rows]
+
+
+def _outputs(kind, M, N, K, seed):
+    """One product's outputs by the tiled kernel, and the same rows in launches of
+    at most 128 (the streaming kernel).  W is any bits: both read the same tiles."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    w = torch.randn(K * N, generator=g, device="cuda").bfloat16() * 0.05
+    splits = G.splits_of(1, N, K)
+    hd, H = 128, N // 3 // 128
+    pos = torch.arange(M, dtype=torch.int32, device="cuda") * 3 % 97
+    kvoff = torch.arange(M, dtype=torch.int64, device="cuda") * N
+    kvoff[::7] = -1
+    qrow = torch.arange(M, dtype=torch.int32, device="cuda")
+    qrow[::5] = -1
+    rcos, rsin = (torch.randn((97, hd // 2), generator=g, device="cuda") for _ in range(2))
+    st = torch.cuda.current_stream().cuda_stream
+    keep = []
+
+    def go(tiled_kernel, r0, rows, outs):
+        mt = G.mcap(rows) // 16
+        xt = _tiled(x[r0:r0 + rows], mt)
+        s = G.GemmShape(None, xt.data_ptr(), mt, rows, w.data_ptr(), N, K, 0, 0, splits)
+        e = G.GemmEpi(kind=kind, ldo=N, o_mtiles=mt, ldq=N // 3, head_stride=hd, H=H, hd=hd)
+        parts = torch.zeros((splits, rows, N), device="cuda")
+        e.part = parts.data_ptr()
+        cols = N // 2 if kind == G.EPI_SWIGLU else N
+        out_t = torch.zeros(mt * 16 * cols, dtype=torch.bfloat16, device="cuda")
+        e.out_t, e.out_f = out_t.data_ptr(), outs[0].data_ptr() + r0 * N * 4
+        e.pos, e.kvoff, e.qrow = (t.data_ptr() + r0 * t.element_size() for t in (pos, kvoff, qrow))
+        e.rcos, e.rsin = rcos.data_ptr(), rsin.data_ptr()
+        e.qout, e.kbase, e.vbase = (o.data_ptr() for o in outs[1:4])
+        keep.extend((xt, parts, out_t))
+        if tiled_kernel:
+            G.launch_wide(s, e, st)
+        else:
+            G.launch(1, s, e, st)
+        if kind in (G.EPI_SILU, G.EPI_SWIGLU):
+            outs[4][r0:r0 + rows, :cols] = _untiled(out_t, mt, cols, rows)
+        elif kind == G.EPI_PARTIAL:
+            one = tiled_kernel and G.wide_sums_slices(M, N, kind)
+            total = parts[0].clone()
+            for i in range(1, splits):  # in slice order
+                total += parts[i]
+            outs[0][r0:r0 + rows] = parts[0] if one else total
+
+    res = []
+    for tiled_kernel in (True, False):
+        outs = [torch.zeros((M, N), device="cuda")]
+        outs += [torch.zeros((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(4)]
+        for r0, rows in [(0, M)] if tiled_kernel else [(r, min(128, M - r)) for r in range(0, M, 128)]:
+            go(tiled_kernel, r0, rows, outs)
+        res.append(outs)
+    torch.cuda.synchronize()
+    return res
+
+
+# every output tile (256x192, 256x128, 256x96, 128x128, 128x96 rows x columns)
+# under every epilogue, whole rounds of the ring and ragged classes (K = 544,
+# 1088: 17 k-blocks a slice), a last row block and a last run of columns in part
+WIDE = [(k, M, N, K, tile) for k in (G.EPI_F32, G.EPI_SILU, G.EPI_SWIGLU, G.EPI_QKV) for M, N, K, tile in (
+    (250, 33792, 512, 0), (250, 26112, 512, 1), (250, 26112, 544, 1), (520, 18432, 512, 1), (250, 18432, 512, 2),
+    (250, 18432, 544, 2), (250, 16128, 512, 3), (250, 16128, 544, 3), (130, 8448, 512, 4), (130, 8448, 544, 4))]
+# slices side by side (128x128, 256x128), and added in registers by one workgroup
+WIDE += [(G.EPI_PARTIAL, M, 4096, K, tile) for K in (1024, 1088) for M, tile in ((250, 3), (1000, 1), (1300, 1))]
+WIDE += [(k, 1300, 4096, K, 1) for k in (G.EPI_F32, G.EPI_SILU) for K in (1024, 1088)]
+
+
+@pytest.mark.parametrize("kind,M,N,K,tile", WIDE)
+def test_every_tile_of_the_wide_kernel_keeps_the_rows_bits(kind, M, N, K, tile):
+    print(f"wide tile {tile} kind={kind} M={M} N={N} K={K}", flush=True)
+    assert G.wide_tile(M, N, K) == tile
+    got, want = _outputs(kind, M, N, K, seed=M + N + K)
+    assert any(bool(w.any()) for w in want)
+    for a, b in zip(got, want):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
 # split reductions of a few rows (slices side by side in one workgroup): two,
