@@ -308,6 +308,7 @@ struct TensorSrc {
 // ---------------------------------------------------------------------------
 // Launch helpers
 // ---------------------------------------------------------------------------
+constexpr char NO_GEMM[] = "no GEMM kernel for this epilogue and shape";
 struct Gemm {
   chimera_ctx* c;
   hipStream_t st;
@@ -340,10 +341,8 @@ struct Gemm {
       c->ev_bytes[c->ev_used] = (double)K * cols * es + (double)M * K * es + (double)M * cols * 4.0;
       c->ev_used++;
     }
-    if (ev)  // the kernels record the events at their own start and end
-      launch_gemm(c->m->dt, s, e, st, ev->a, ev->b);
-    else
-      launch_gemm(c->m->dt, s, e, st);
+    // the kernels record the events at their own start and end
+    REQUIRE(launch_gemm(c->m->dt, s, e, st, ev ? ev->a : nullptr, ev ? ev->b : nullptr), CHIMERA_EINVAL, NO_GEMM);
   }
 };
 
@@ -1626,7 +1625,7 @@ chimera_status chimera_debug_gemm(int32_t dtype, const void* x, const void* w, i
       e.out_f = (float*)dy;
       e.ldo = N;
       e.part = (float*)ds;
-      launch_gemm(dtype, s, e, nullptr);
+      REQUIRE(launch_gemm(dtype, s, e, nullptr), CHIMERA_EINVAL, NO_GEMM);
       HIPCK(hipGetLastError());
       HIPCK(hipDeviceSynchronize());
       HIPCK(hipMemcpy(y, dy, (size_t)M * N * 4, hipMemcpyDeviceToHost));
@@ -1710,7 +1709,7 @@ chimera_status chimera_gemm_static(int32_t dtype, const void* x, const void* w, 
     e.out_f = y;
     e.ldo = N;
     e.part = (float*)(base + xb + wb);
-    launch_gemm(dtype, s, e, st);
+    REQUIRE(launch_gemm(dtype, s, e, st), CHIMERA_EINVAL, NO_GEMM);
     HIPCK(hipGetLastError());
   });
 }

@@ -21,8 +21,6 @@ __device__ __forceinline__ void epi_elem(const GemmEpi& e, int kind, int N, int 
     e.part[((int64_t)split * M + row) * N + col] = v;
   } else if (kind == EPI_F32) {
     e.out_f[(int64_t)row * e.ldo + col] = v;
-  } else if (kind == EPI_T) {
-    store_tiled<T>((T*)e.out_t, e.o_mtiles, row, col, v);
   } else if (kind == EPI_SILU) {
     store_tiled<T>((T*)e.out_t, e.o_mtiles, row, col, silu_f(v));
   } else if (kind == EPI_SWIGLU) {

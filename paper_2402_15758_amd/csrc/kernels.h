@@ -20,13 +20,13 @@ enum { PACK_NATURAL = 0, PACK_QKV = 1, PACK_GU = 2 };
 
 // EPI_ZIN (gemm_rows_takes launches only): the draft's residual add into the
 // second half of a head MLP's input, tiled out_t[row][N + col] = T(out_f[row][col] + v).
-enum { EPI_F32 = 0, EPI_T = 1, EPI_SILU = 2, EPI_SWIGLU = 3, EPI_QKV = 4, EPI_PARTIAL = 5, EPI_ZIN = 6 };
+enum { EPI_F32 = 0, EPI_SILU = 2, EPI_SWIGLU = 3, EPI_QKV = 4, EPI_PARTIAL = 5, EPI_ZIN = 6 };
 
 struct GemmEpi {
   int kind = EPI_F32;
   float* out_f = nullptr;  // EPI_F32: row-major [M][ldo]
   int ldo = 0;
-  void* out_t = nullptr;   // EPI_T / EPI_SILU / EPI_SWIGLU: tiled storage-type output
+  void* out_t = nullptr;   // EPI_SILU / EPI_SWIGLU / EPI_ZIN: tiled storage-type output
   int o_mtiles = 0;        //   with this many 16-row tiles
   float* part = nullptr;   // EPI_PARTIAL: [splits][M][N] (packed column order); other
                            // epilogues with split-K: scratch of the same shape
@@ -88,7 +88,8 @@ int gemm_wide_tile(int M, int nbc, int kps, int splits);
 void launch_gemm_wide(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb);
 // ev_start / ev_stop (optional): recorded by the dispatch of the GEMM's
 // first and last kernel (hipExtLaunchKernel), i.e. the kernel execution span.
-void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start = nullptr,
+// false, and nothing launched: no kernel serves this epilogue on this shape.
+bool launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start = nullptr,
                  hipEvent_t ev_stop = nullptr);
 void launch_repack(int dtype, int kind, const void* src0, const void* src1, const void* src2, int K, int n_src,
                    void* dst, int H, int hd, hipStream_t st);

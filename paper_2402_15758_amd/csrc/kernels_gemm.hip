@@ -618,12 +618,16 @@ int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles) {
   return splits;
 }
 
-void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start,
+bool launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start,
                  hipEvent_t ev_stop) {
-  if (s.M <= 0) return;
+  if (s.M <= 0) return true;
   if (gemm_rows_takes(dtype, s.M, gemm_blocks(s), s.K, s.splits, e.kind)) {
     launch_gemm_rows(dtype, s, e, st, ev_start, ev_stop);
-    return;
+    return true;
+  }
+  switch (e.kind) {
+    case EPI_F32: case EPI_SILU: case EPI_SWIGLU: case EPI_QKV: case EPI_PARTIAL: break;
+    default: return false;  // EPI_ZIN is for launches of a few rows
   }
   if (gemm_wide_takes(dtype, s.M, gemm_blocks(s), s.K, s.splits, s.x_mtiles)) {
     const bool finish = s.splits > 1 && e.kind != EPI_PARTIAL && !gemm_wide_sums_slices(s.M, gemm_blocks(s), e.kind);
@@ -637,12 +641,13 @@ void launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st
     } else {
       launch_gemm_wide(s, e, st, ev_start, ev_stop);
     }
-    return;
+    return true;
   }
   if (dtype == DT_BF16)
     gemm_t<bf16_t>(s, e, st, ev_start, ev_stop);
   else
     gemm_t<float>(s, e, st, ev_start, ev_stop);
+  return true;
 }
 
 void launch_repack(int dtype, int kind, const void* src0, const void* src1, const void* src2, int K, int n_src,

@@ -452,7 +452,7 @@ void launch_gemm_wide(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipE
     go_unsplit<EPI_SILU>(s, e, st, ea, eb);
   } else if (e.kind == EPI_SWIGLU) {
     go_unsplit<EPI_SWIGLU>(s, e, st, ea, eb);
-  } else {
+  } else if (e.kind == EPI_QKV) {  // launch_gemm refuses every other kind
     go_unsplit<EPI_QKV>(s, e, st, ea, eb);
   }
 }

@@ -64,12 +64,12 @@ def wide_sums_slices(M, cols, kind):
 
 def _launch(f, lead, shape, epi, stream):
     f.argtypes = [ctypes.c_int] * len(lead) + [ctypes.c_void_p] * 5
-    f(*lead, ctypes.addressof(shape), ctypes.addressof(epi), stream, None, None)
+    return f(*lead, ctypes.addressof(shape), ctypes.addressof(epi), stream, None, None)
 
 
 def launch(bf16, shape, epi, stream):
-    _launch(fn("_Z11launch_gemmiRK9GemmShapeRK7GemmEpiP12ihipStream_tP11ihipEvent_tS8_", None), (bf16,), shape, epi,
-            stream)
+    return _launch(fn("_Z11launch_gemmiRK9GemmShapeRK7GemmEpiP12ihipStream_tP11ihipEvent_tS8_", ctypes.c_bool), (bf16,),
+                   shape, epi, stream)
 
 
 def launch_wide(shape, epi, stream):

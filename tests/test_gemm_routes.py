@@ -2,7 +2,8 @@
 rules of kernels.h, called in the built library (no GPU)."""
 import pytest
 
-from gemm_launch import (EPI_F32, EPI_PARTIAL, EPI_SILU, EPI_ZIN, rows_takes, stream_plan, wide_takes)
+from gemm_launch import (EPI_F32, EPI_PARTIAL, EPI_SILU, EPI_ZIN, GemmEpi, GemmShape, launch, mcap, rows_takes,
+                         splits_of, stream_plan, wide_takes)
 from paper_2402_15758_amd import binding as B
 
 
@@ -54,3 +55,14 @@ def test_few_row_launches_where_one_workgroup_a_block_is_faster(bf16, M, cols, K
 def test_wide_launches_run_on_the_faster_kernel(M, cols, K, tiled):
     assert wide_takes(1, M, cols, K) == tiled
     assert not wide_takes(0, M, cols, K)
+
+
+# An epilogue that no kernel of a launch's route applies is refused before any
+# launch (there is no GPU here): the few-row epilogue on more rows or an unsplit
+# matrix, and values that name none.
+@pytest.mark.parametrize("kind", [EPI_ZIN, 1, 7, -1])
+@pytest.mark.parametrize("bf16,M,N,K", [(1, 17, 4096, 11008), (1, 256, 4096, 11008), (1, 256, 22016, 4096),
+                                        (0, 300, 256, 768), (1, 1, 16384, 4096)])
+def test_an_epilogue_without_a_kernel_is_refused(kind, bf16, M, N, K):
+    s = GemmShape(M=M, N=N, K=K, x_mtiles=mcap(M) // 16, splits=splits_of(bf16, N, K))
+    assert launch(bf16, s, GemmEpi(kind=kind), None) is False

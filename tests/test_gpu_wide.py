@@ -89,7 +89,7 @@ def _outputs(kind, M, N, K, seed):
         if tiled_kernel:
             G.launch_wide(s, e, st)
         else:
-            G.launch(1, s, e, st)
+            assert G.launch(1, s, e, st)
         if kind in (G.EPI_SILU, G.EPI_SWIGLU):
             outs[4][r0:r0 + rows, :cols] = _untiled(out_t, mt, cols, rows)
         elif kind == G.EPI_PARTIAL:
