@@ -719,8 +719,9 @@ void carve_ctx(chimera_ctx* c, Arena& a) {
   const size_t es = m->es, d = cf.d_model, F = cf.d_ffn, V = cf.vocab, H = cf.n_heads, hd = cf.head_dim;
   const size_t B = c->B, K = c->K, Mv = c->Mv, Md = c->Md, N = c->N, Mq = c->Mq;
   const size_t Qp = (size_t)mcap(c->Mq);
-  // prefill chunks run through the verify and draft-row buffers too
-  const size_t Mp = c->Mp, Px = std::max(Mv, Mp), Pd = std::max(Md, Mp), Pe = std::max(Md, 2 * Mp);
+  // prefill chunks run through the verify buffers and, with a draft, its rows' too
+  const size_t Mp = c->Mp, Px = std::max(Mv, Mp);
+  const size_t Pd = K > 0 ? std::max(Md, Mp) : Md, Pe = K > 0 ? std::max(Md, 2 * Mp) : Md;
   const size_t nblk_pf = Mp / 64 + B;  // attention blocks of a chunk: each sequence may end one early
   c->mt_v = (int)(Mv / 16);
   c->mt_d = (int)(Md / 16);
@@ -756,24 +757,26 @@ void carve_ctx(chimera_ctx* c, Arena& a) {
   c->q = a.take(Px * d * es);
   c->attn = a.take(Px * d * es);
   c->hbuf = a.take(Px * F * es);
-  const size_t max_parts = std::max(gemm_pick_splits((int)d, (int)(H * hd), m->dt), gemm_pick_splits((int)d, (int)F, m->dt));
-  c->parts = a.arr<float>(max_parts * Px * d);
-  // split-K scratch: the largest splits * M * N_full over the launches this
-  // context makes (partials are indexed with the full packed width)
-  size_t scr = 1;
-  auto need = [&](size_t M, int cols, int n_full, int Kd) {
-    const int s = gemm_pick_splits(cols, Kd, m->dt);
-    if (s > 1) scr = std::max(scr, (size_t)s * M * (size_t)n_full);
-  };
   const int hdim = (int)(H * hd);
-  for (size_t M : {Px, Pe, Qp, (size_t)128}) {
-    need(M, 3 * hdim, 3 * hdim, (int)d);
-    need(M, 2 * hdim, 3 * hdim, (int)d);
-    need(M, 2 * (int)F, 2 * (int)F, (int)d);
-    need(M, (int)V, (int)V, (int)d);
-    need(M, (int)d, (int)d, 3 * (int)d);
-    need(M, (int)d, (int)d, (int)d);
-    need(M, (int)d, (int)d, 2 * (int)d);
+  c->parts = a.arr<float>(d * std::max(gemm_partial_rows(m->dt, (int)Px, (int)d, hdim, EPI_PARTIAL),
+                                       gemm_partial_rows(m->dt, (int)Px, (int)d, (int)F, EPI_PARTIAL)));
+  // split-K scratch: the most that a launch of this context leaves to a
+  // finishing pass (partials are indexed with the full packed width)
+  size_t scr = 1;
+  auto need = [&](size_t M, int cols, int n_full, int Kd, int kind) {
+    scr = std::max(scr, (size_t)gemm_partial_rows(m->dt, (int)M, cols, Kd, kind) * n_full);
+  };
+  need(Px, 3 * hdim, 3 * hdim, (int)d, EPI_QKV);
+  need(Px, 2 * (int)F, 2 * (int)F, (int)d, EPI_SWIGLU);
+  need(Mv, (int)V, (int)V, (int)d, EPI_F32);
+  if (K > 0) {
+    need(Pd, (int)d, (int)d, 3 * (int)d, EPI_SILU);
+    need(Pd, (int)d, (int)d, (int)d, EPI_F32);
+    need(Md, 3 * hdim, 3 * hdim, (int)d, EPI_QKV);
+    need(Pe, 2 * hdim, 3 * hdim, (int)d, EPI_QKV);
+    need(Qp, 2 * (int)F, 2 * (int)F, (int)d, EPI_SWIGLU);
+    need(Qp, (int)d, (int)d, 2 * (int)d, EPI_SILU);
+    need(Qp, (int)V, (int)V, (int)d, EPI_F32);
   }
   c->scratch = a.arr<float>(scr);
   c->logits = a.arr<float>(Mv * V);

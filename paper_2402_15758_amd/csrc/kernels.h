@@ -70,9 +70,12 @@ struct StreamPlan {
   int row_tiles, row_blocks, runs, run, long_runs, mapped;
 };
 StreamPlan gemm_stream_plan(int M, int nbc, int splits, int x_mtiles);
-// Partials [parts][M][N] that an EPI_PARTIAL launch writes: its slices, or 1
-// where a launch of many rows adds them (in slice order) itself.
-int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles);
+// Partials [parts][M][N] that a launch writes to e.part.  EPI_PARTIAL: its
+// slices, or 1 where a launch of many rows adds them (in slice order) itself.
+// Other epilogues: what a finishing pass reads, 0 where there is none.
+int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles, int kind = EPI_PARTIAL);
+// The largest parts * M over launches of 1 to max_M rows.
+int64_t gemm_partial_rows(int dtype, int max_M, int n_cols, int K, int kind);
 // Split launches of a few rows (kernels_gemm_rows.hip): all slices in one
 // workgroup per column block, the epilogue on the whole sum.
 bool gemm_rows_takes(int dtype, int M, int nbc, int K, int splits, int kind);
@@ -80,6 +83,7 @@ void launch_gemm_rows(int dtype, const GemmShape& s, const GemmEpi& e, hipStream
 // Launches of many rows (kernels_gemm_wide.hip, bf16): the same sums on 2-D
 // output tiles.  sums_slices: the launch applies its epilogue to the whole
 // sum; otherwise a split launch writes one partial per slice.
+bool gemm_wide_fits(int K, int x_mtiles);  // its offsets are 32-bit
 bool gemm_wide_takes(int dtype, int M, int nbc, int K, int splits, int x_mtiles);
 bool gemm_wide_sums_slices(int M, int nbc, int kind);
 // Output tile of such a launch, kps k-blocks a slice: 0 256x192, 1 256x128, 2

@@ -612,10 +612,28 @@ int gemm_pick_splits(int n_cols, int K, int dtype) {
   return s;
 }
 
-int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles) {
+int gemm_partials(int dtype, int M, int n_cols, int K, int x_mtiles, int kind) {
   const int splits = gemm_pick_splits(n_cols, K, dtype), nbc = n_cols / 16;
-  if (gemm_wide_takes(dtype, M, nbc, K, splits, x_mtiles) && gemm_wide_sums_slices(M, nbc, EPI_PARTIAL)) return 1;
+  if (kind != EPI_PARTIAL && (splits == 1 || gemm_rows_takes(dtype, M, nbc, K, splits, kind))) return 0;
+  if (gemm_wide_takes(dtype, M, nbc, K, splits, x_mtiles)) {
+    if (kind != EPI_PARTIAL && gemm_wide_sums_slices(M, nbc, kind)) return 0;
+    if (gemm_wide_sums_slices(M, nbc, EPI_PARTIAL)) return 1;
+  }
   return splits;
+}
+
+int64_t gemm_partial_rows(int dtype, int max_M, int n_cols, int K, int kind) {
+  // A buffer of over 4 GiB keeps all its launches on the streaming kernel;
+  // below that the route of more than 16 rows depends on whole 64-row blocks
+  // alone, so the last row of each block stands for it.
+  const int mtiles = (max_M + 127) / 128 * 8;
+  int64_t most = 0;
+  for (int M = std::min(64, max_M); M > 0; M = M == max_M ? 0 : std::min(M + 64, max_M)) {
+    const bool huge = !gemm_wide_fits(K, mtiles);
+    const int parts = huge ? gemm_pick_splits(n_cols, K, dtype) : gemm_partials(dtype, M, n_cols, K, mtiles, kind);
+    most = std::max(most, (int64_t)parts * M);
+  }
+  return most;
 }
 
 bool launch_gemm(int dtype, const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ev_start,

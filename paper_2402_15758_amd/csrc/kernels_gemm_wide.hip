@@ -419,10 +419,12 @@ void go_slices(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t 
 
 }  // namespace
 
+bool gemm_wide_fits(int K, int x_mtiles) { return (int64_t)K * 16 * x_mtiles * 2 < (int64_t)1 << 32 && K < 1 << 24; }
+
 bool gemm_wide_takes(int dtype, int M, int nbc, int K, int splits, int x_mtiles) {
   // up to 128 rows the streaming kernel is faster (QKV at 128 rows 33 us
-  // against 37 us); this kernel's K offsets are 32-bit
-  if (dtype != DT_BF16 || M <= 128 || (int64_t)K * 16 * x_mtiles * 2 >= (int64_t)1 << 32 || K >= 1 << 24) return false;
+  // against 37 us)
+  if (dtype != DT_BF16 || M <= 128 || !gemm_wide_fits(K, x_mtiles)) return false;
   // Matrices too small for its tiles to reach most CUs, and those whose
   // columns the streaming kernel deals in shorter runs, stay on that one, us:
   // 256 rows 768 x 256 3.8 / 5.8, 1024 x 4096 14.7 / 15.6, 8192 x 4096 30.6 /

@@ -58,6 +58,14 @@ def wide_tile(M, cols, K):
     return fn("_Z14gemm_wide_tileiiii", ctypes.c_int)(M, cols // 16, K // 32 // s, s)
 
 
+def partials(bf16, M, cols, K, kind, mtiles):
+    return fn("_Z13gemm_partialsiiiiii", ctypes.c_int)(bf16, M, cols, K, mtiles, kind)
+
+
+def partial_rows(bf16, max_M, cols, K, kind):
+    return fn("_Z17gemm_partial_rowsiiiii", ctypes.c_int64)(bf16, max_M, cols, K, kind)
+
+
 def wide_sums_slices(M, cols, kind):
     return fn("_Z21gemm_wide_sums_slicesiii", ctypes.c_bool)(M, cols // 16, kind)
 

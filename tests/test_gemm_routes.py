@@ -2,8 +2,8 @@
 rules of kernels.h, called in the built library (no GPU)."""
 import pytest
 
-from gemm_launch import (EPI_F32, EPI_PARTIAL, EPI_SILU, EPI_ZIN, GemmEpi, GemmShape, launch, mcap, rows_takes,
-                         splits_of, stream_plan, wide_takes)
+from gemm_launch import (EPI_F32, EPI_PARTIAL, EPI_QKV, EPI_SILU, EPI_SWIGLU, EPI_ZIN, GemmEpi, GemmShape, launch,
+                         mcap, partial_rows, partials, rows_takes, splits_of, stream_plan, wide_takes)
 from paper_2402_15758_amd import binding as B
 
 
@@ -66,3 +66,26 @@ def test_wide_launches_run_on_the_faster_kernel(M, cols, K, tiled):
 def test_an_epilogue_without_a_kernel_is_refused(kind, bf16, M, N, K):
     s = GemmShape(M=M, N=N, K=K, x_mtiles=mcap(M) // 16, splits=splits_of(bf16, N, K))
     assert launch(bf16, s, GemmEpi(kind=kind), None) is False
+
+
+# The workspace of split launches holds every launch of up to max_M rows (the
+# input buffer's tiles may exceed a launch's own), and no more than one of them uses
+@pytest.mark.parametrize("bf16,cols,K", [(1, 4096, 4096), (1, 4096, 11008), (1, 256, 768), (1, 768, 4096),
+                                         (1, 6144, 1024), (1, 5120, 13824), (1, 12288, 4096), (0, 1024, 3072)])
+@pytest.mark.parametrize("kind", [EPI_PARTIAL, EPI_F32, EPI_SILU, EPI_SWIGLU, EPI_QKV])
+def test_the_split_workspace_covers_every_launch(bf16, cols, K, kind):
+    for max_M in (1, 16, 17, 63, 128, 300, 2048):
+        most = 0
+        for M in range(1, max_M + 1):
+            rows = {M * partials(bf16, M, cols, K, kind, t // 16) for t in (mcap(M), mcap(max_M))}
+            assert len(rows) == 1
+            most = max(most, rows.pop())
+        assert partial_rows(bf16, max_M, cols, K, kind) == most
+
+
+def test_the_split_workspace_of_a_chunk_is_what_its_launches_leave():
+    # 7B: a 2048-row chunk's O and down projections add their slices themselves
+    # from 1281 rows on, the trigram products too
+    assert partial_rows(1, 2048, 4096, 4096, EPI_PARTIAL) <= 4 * 1280
+    assert partial_rows(1, 2048, 4096, 12288, EPI_SILU) <= 4 * 1280
+    assert partial_rows(1, 2048, 12288, 4096, EPI_QKV) == 0

@@ -232,3 +232,21 @@ def test_step_graph_survives_a_prefill_of_the_same_batch():
                 assert all(np.array_equal(a, b) for a, b in zip(got, want))
         graph.close()
         eager.close()
+
+
+def test_a_context_without_a_draft_holds_no_draft_rows():
+    """A one-node context fills no draft memory in a prefill: of the chunk's
+    draft rows (2048 trigram inputs and hidden rows, 4096 encoder inputs in
+    float32 and storage type with their descriptors) it holds those of a step."""
+    print("context bytes", flush=True)
+    cfg = synth.small_config()
+    w = synth.make_weights(cfg, device="cuda")
+    draft = Session(cfg, w, synth.TREE_T8, max_batch=1, max_len=4096)
+    plain = Session(cfg, None, (), max_batch=1, max_len=4096, share_model=draft)
+    d, step = cfg.d_model, 128
+    chunk = (2048 - step) * 4 * d * 2 + (4096 - step) * (d * (4 + 2) + 4 + 8 + 4)
+    assert draft.ctx_arena.numel() - plain.ctx_arena.numel() >= chunk
+    prompt = synth.make_prompt(2500, cfg.vocab, 3)
+    assert int(plain.prefill([prompt])[0]) == int(draft.prefill([prompt])[0])
+    for s in (plain, draft):
+        s.close()
