@@ -305,7 +305,9 @@ chimera_status chimera_debug_gemm(int32_t dtype, const void* x, const void* w, i
  * allocation, no free and no synchronisation.
  *   x: device [M][K] row-major, w: device [K][N] row-major, both of `dtype`
  *   (caller-owned, only read); y: device float32 [M][N] row-major
- *   (caller-owned, written); stream: hipStream_t or NULL.
+ *   (caller-owned, written); stream: hipStream_t or NULL.  x, w and y may
+ *   start at any element of their type (16-byte boundaries are fastest for x
+ *   and w).
  * The call only enqueues its kernels on `stream`.  Its scratch -- the tiled
  * copy of x, the repacked copy of w and the split-K partials -- is a 32 MiB
  * static device array that every device holds until the process ends:

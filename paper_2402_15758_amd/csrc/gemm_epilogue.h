@@ -8,6 +8,10 @@ namespace {
 
 constexpr int NB = 4;  // 16-column blocks per weight-layout group
 
+// Four floats of a row-major output, which may be a caller's and start at any
+// float: still one 16-byte store (global stores take 4-byte alignment).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
 // ---------------------------------------------------------------------------
 // Epilogue of one output element: v is packed column 16 blk + c16 of `row`,
 // vp the same row's value at lane column c16 ^ 8 (the other half of a rotary
@@ -125,8 +129,8 @@ __device__ __forceinline__ void store_tile(const GemmShape& sh, const GemmEpi& e
     for (int r = 0; r < 4; ++r) tw[(4 * g + r) * 16 + c16] = v[r];
     __builtin_amdgcn_wave_barrier();
     const int row = 16 * mb + (lane >> 2);
-    const float4 o = *reinterpret_cast<const float4*>(tw + (lane >> 2) * 16 + 4 * (lane & 3));
-    if (row < sh.M) *reinterpret_cast<float4*>(base + (int64_t)row * ld + 16 * blk + 4 * (lane & 3)) = o;
+    const f32x4 o = *reinterpret_cast<const f32x4*>(tw + (lane >> 2) * 16 + 4 * (lane & 3));
+    if (row < sh.M) *reinterpret_cast<f32x4_any*>(base + (int64_t)row * ld + 16 * blk + 4 * (lane & 3)) = o;
     __builtin_amdgcn_wave_barrier();
     return;
   }

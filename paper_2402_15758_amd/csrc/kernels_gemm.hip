@@ -209,8 +209,8 @@ __device__ __forceinline__ void gemm_epilogue(const GemmShape& sh, const GemmEpi
       for (int r = 0; r < 4; ++r) tw[(4 * g + r) * 16 + c16] = vv[k][r];
       __builtin_amdgcn_wave_barrier();
       const int row = 16 * (mb0 + i) + (lane >> 2);
-      const float4 v = *reinterpret_cast<const float4*>(tw + (lane >> 2) * 16 + 4 * (lane & 3));
-      if (row < sh.M) *reinterpret_cast<float4*>(base + (int64_t)row * ld + 16 * blk + 4 * (lane & 3)) = v;
+      const f32x4 v = *reinterpret_cast<const f32x4*>(tw + (lane >> 2) * 16 + 4 * (lane & 3));
+      if (row < sh.M) *reinterpret_cast<f32x4_any*>(base + (int64_t)row * ld + 16 * blk + 4 * (lane & 3)) = v;
       __builtin_amdgcn_wave_barrier();
     }
     return;

@@ -178,6 +178,26 @@ def test_static_gemm_stages_any_alignment(dtype, M, N, K, shift):
     assert np.array_equal(y.cpu().numpy().view(np.uint32), want.view(np.uint32))
 
 
+# y may start at any float, on every route: a few rows with their slices in one
+# workgroup, the streaming kernel unsplit and with its finishing pass, the tiled one
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 16, 64, 1024), ("bf16", 40, 8192, 64), ("f32", 40, 64, 1024),
+                                         ("bf16", 129, 8256, 160)])
+@pytest.mark.parametrize("shift", [1, 2, 3])
+def test_static_gemm_stores_from_any_float(dtype, M, N, K, shift):
+    print(f"static gemm y {dtype} M={M} N={N} K={K} shift={shift}", flush=True)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    dt = B.CHIMERA_F32 if dtype == "f32" else B.CHIMERA_BF16
+    g = torch.Generator().manual_seed(M + N + K)
+    x = torch.randn((M, K), generator=g).to(tdt).cuda()
+    w = torch.randn((K, N), generator=g).to(tdt).cuda()
+    want = torch.zeros((M, N), dtype=torch.float32, device="cuda")
+    buf = torch.full((M * N + 8,), 7.0, dtype=torch.float32, device="cuda")
+    for y in (want.data_ptr(), buf.data_ptr() + 4 * shift):
+        B.chimera_gemm_static(dt, x.data_ptr(), w.data_ptr(), M, N, K, y, torch.cuda.current_stream().cuda_stream)
+    assert torch.equal(buf[shift:shift + M * N].view(torch.int32), want.view(-1).view(torch.int32))
+    assert bool((buf[:shift] == 7).all()) and bool((buf[shift + M * N:] == 7).all())
+
+
 def _states(sess):
     """What two steps after the prefill show of every sequence."""
     out = [[] for _ in range(sess.batch)]
