@@ -6,7 +6,7 @@ Two kinds of run are summarised (commands as recorded in each summary):
                 python3 bench.py --workload WL [bench flags]
             -> profiles/step_kernels_WL.md: per-step kernel table of the timed
                (graph-replayed) pass, step/draft/verify/tail spans between the
-               step's wall-clock stamp kernels, and the verify GEMM launches of
+               step's wall-clock stamps, and the verify GEMM launches of
                the timed and the eager (event-timed) pass, per GEMM role.
 
   counters  rocprofv3 --pmc <counters> --output-format csv -d DIR/<name> -o run --
@@ -17,8 +17,8 @@ Two kinds of run are summarised (commands as recorded in each summary):
             -> profiles/counters_WL.md, and for the 7B 512-token workload the
                record bench.py reads (verify_gemm_llama7b_p512_traffic.json).
 
-Steps are found through the stamp kernels every decode step launches (four
-per step: draft start, verify start, verify end, step end).  A speculative
+Steps are found through the kernels that take a decode step's wall-clock stamps
+(draft start, verify start, verify end, and the stamp kernel that ends it).  A speculative
 step is told from a plain greedy one by its verify GEMMs covering more than one
 16-row tile block.  The byte counters are scaled by what they read for the
 sample's three 1 GiB device copies (2^20 KiB read and 2^20 KiB written).
@@ -52,8 +52,9 @@ OUT_DIR = os.environ.get("PROFILES_DIR", os.path.join(ROOT, "profiles"))
 HBM_PEAK = 8.0e12
 BF16_PEAK = 2.5e15
 GEMM_SOURCES = ["paper_2402_15758_amd/csrc/kernels_gemm.hip", "paper_2402_15758_amd/csrc/kernels_gemm_wide.hip",
-                "paper_2402_15758_amd/csrc/gemm_epilogue.h", "paper_2402_15758_amd/csrc/common.h",
-                "paper_2402_15758_amd/csrc/kernels.h", "paper_2402_15758_amd/build.py"]
+                "paper_2402_15758_amd/csrc/kernels_gemm_rows.hip", "paper_2402_15758_amd/csrc/gemm_epilogue.h",
+                "paper_2402_15758_amd/csrc/common.h", "paper_2402_15758_amd/csrc/kernels.h",
+                "paper_2402_15758_amd/build.py"]
 GEMM_RE = re.compile(r"gemm_kernel<[^,]+, (\d+), (\d+)")
 WIDE_RE = re.compile(r"gemm_wide_kernel<[^,]+, \d+, (\d+), \d+, (\d+)")
 
@@ -68,6 +69,8 @@ def gemm_mb(name):
     m = GEMM_RE.search(name)
     if m:
         return int(m.group(1))
+    if "gemm_rows_kernel<" in name:
+        return 1
     m = WIDE_RE.search(name)
     return int(m.group(1)) * int(m.group(2)) if m else 0
 

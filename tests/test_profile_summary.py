@@ -83,6 +83,20 @@ def test_gemm_counters_scaled_by_copies_and_matched_to_roles(tmp_path, monkeypat
     assert row.split("|")[3].strip() == str(2 * wl.model.n_layers)  # two steps, one QKV per layer
 
 
+@pytest.mark.parametrize("name,tiles", [
+    ("gemm_kernel<unsigned short, 4, 8, true>", 4), ("gemm_rows_kernel<unsigned short, 0, 16>", 1),
+    ("gemm_wide_kernel<unsigned short, 5, 4, 2, 4, 6, 4, false, true>", 16), ("rmsnorm_kernel<unsigned short>", 0),
+    ("gemm_finish_kernel<unsigned short>", 0)])
+def test_every_gemm_kernel_is_recognised(name, tiles):
+    assert ps.gemm_mb(f"void (anonymous namespace)::{name}(GemmShape, GemmEpi, int)") == tiles
+
+
+def test_every_gemm_source_is_in_the_record():
+    import paper_2402_15758_amd.build as build
+    names = [os.path.basename(s) for s in ps.GEMM_SOURCES]
+    assert all(s in names for s in build.SOURCES if s.startswith("kernels_gemm"))
+
+
 def test_gemm_counters_refuse_a_layer_count_mismatch(tmp_path, monkeypatch):
     monkeypatch.setattr(ps, "OUT_DIR", str(tmp_path))
     wl = synth.WORKLOADS["llama7b_p512"]
