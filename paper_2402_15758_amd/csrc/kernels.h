@@ -266,6 +266,7 @@ void launch_typical_stats(const float* logits, int rows, int V, int N, int b0, c
 void launch_argmax(const float* logits, int M, int V, int* amax, hipStream_t st);
 // Per query row r of level lv: the top-s list of z = logits + r * ld into
 // cand[b][node] (forced as set up in s).  scratch: [B*R][32][8] values and ids.
+int topk_splits(int V);  // workgroups that share a row
 void launch_topk(const float* logits, int64_t ld, const StepState& s, const DraftLevel& lv, float* scratch_v,
                  int* scratch_i, hipStream_t st);
 // Start of the verify pass: tree tokens, row descriptors, window rows and the

@@ -230,9 +230,11 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const float* __restrict__ 
 // Stage 1: TOPK_SPLIT workgroups per sequence keep the best S ids of their
 // slice (excluding the reference id); stage 2 merges them.
 constexpr int TOPK_SPLIT = 32;
-// Up to this vocabulary one workgroup scans a row and writes the list itself
-// (at 1024 entries the merge launch is half of the time).
-constexpr int TOPK_ONE = 4096;
+// Up to this vocabulary one workgroup scans a row and writes the list itself: a
+// thread's scan grows with the row, the merge launch does not.  A step of four
+// draft levels, one workgroup / slices and merge, us: 256 entries 255 / 268,
+// 1024 269 / 275, 1536 276 / 276, 2048 280 / 275, 4096 300 / 275.
+constexpr int TOPK_ONE = 1536;
 constexpr int SMAX = 8;
 
 __device__ __forceinline__ int forced_ref(const StepState& s, int b, int level, int V, bool* ok) {
@@ -1053,13 +1055,14 @@ void launch_argmax(const float* logits, int M, int V, int* amax, hipStream_t st)
   hipLaunchKernelGGL(argmax_kernel, dim3(M), dim3(1024), 0, st, logits, V, amax);
 }
 
+int topk_splits(int V) { return V <= TOPK_ONE ? 1 : TOPK_SPLIT; }
+
 void launch_topk(const float* logits, int64_t ld, const StepState& s, const DraftLevel& lv, float* scratch_v,
                  int* scratch_i, hipStream_t st) {
   const int Q = s.B * lv.R;
-  const bool one = s.V <= TOPK_ONE;
-  hipLaunchKernelGGL(topk_partial_kernel, dim3(one ? 1 : TOPK_SPLIT, Q), dim3(256), 0, st, logits, ld, s, lv, scratch_v,
-                     scratch_i);
-  if (one) return;
+  const int splits = topk_splits(s.V);
+  hipLaunchKernelGGL(topk_partial_kernel, dim3(splits, Q), dim3(256), 0, st, logits, ld, s, lv, scratch_v, scratch_i);
+  if (splits == 1) return;
   hipLaunchKernelGGL(topk_merge_kernel, dim3(Q), dim3(64), 0, st, s, lv, (const float*)scratch_v,
                      (const int*)scratch_i);
 }

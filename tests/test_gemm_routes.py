@@ -1,9 +1,12 @@
-"""Which kernel a GEMM launch runs on and how it is dealt out: the host-side
-rules of kernels.h, called in the built library (no GPU)."""
+"""Which kernel a GEMM launch runs on and how it is dealt out, and how a top-s
+selection is: the host-side rules of kernels.h, called in the built library (no
+GPU)."""
+import ctypes
+
 import pytest
 
 from gemm_launch import (EPI_F32, EPI_PARTIAL, EPI_QKV, EPI_SILU, EPI_SWIGLU, EPI_ZIN, GemmEpi, GemmShape, launch,
-                         mcap, partial_rows, partials, rows_takes, splits_of, stream_plan, wide_takes)
+                         fn, mcap, partial_rows, partials, rows_takes, splits_of, stream_plan, wide_takes)
 from paper_2402_15758_amd import binding as B
 
 
@@ -89,3 +92,8 @@ def test_the_split_workspace_of_a_chunk_is_what_its_launches_leave():
     assert partial_rows(1, 2048, 4096, 4096, EPI_PARTIAL) <= 4 * 1280
     assert partial_rows(1, 2048, 4096, 12288, EPI_SILU) <= 4 * 1280
     assert partial_rows(1, 2048, 12288, 4096, EPI_QKV) == 0
+
+
+def test_top_s_rows_are_shared_where_one_workgroup_is_slower():
+    splits = fn("_Z11topk_splitsi", ctypes.c_int)
+    assert [splits(V) for V in (64, 1024, 1536, 1600, 2048, 4096, 32000)] == [1, 1, 1, 32, 32, 32, 32]
