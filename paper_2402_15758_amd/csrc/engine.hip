@@ -636,7 +636,13 @@ void prefill_chunk(chimera_ctx* c, const StepState& s, const PrefillChunk& ch, c
   for (int k = 0; k < ch.n_seg; ++k) nblk += (ch.row0[k + 1] - ch.row0[k] + 63) / 64;
   launch_prefill_rows(dt, s, m->embed, ch, c->pf_tokens, c->pf_blk, draft, c->tri_in, mt, c->d_pos, c->d_kvoff,
                       c->d_qrow, st);
-  VerifyRows r{c->pf_tokens, M, nullptr, kv->page_table, c->chain.depth, c->chain.path, 64, 63, nblk, mt, c->pf_blk};
+  VerifyRows r{};
+  r.tokens = c->pf_tokens;
+  r.M = M;
+  r.page_table = kv->page_table;
+  r.B = nblk;
+  r.mtiles = mt;
+  r.blk = c->pf_blk;
   verify_layers(c, r, st, false);
   if (draft) {
     // target-state entries (rows [0, M)) and trigram entries (rows [M, 2M))

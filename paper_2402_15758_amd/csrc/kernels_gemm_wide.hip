@@ -1,5 +1,5 @@
-// GEMMs of more than 128 bf16 rows (prefill chunks, wide verify batches):
-// Y = X[M][K] @ W[K][N] on 2-D output tiles, with the operands of
+// GEMMs of more than 128 bf16 rows (prefill chunks, wide verify batches) over
+// matrices wide or deep enough: Y = X[M][K] @ W[K][N] on 2-D output tiles, with the operands of
 // kernels_gemm.hip (both in MFMA fragment order) and its summation order, bit
 // for bit: per reduction slice four partial sums, one per residue class of the
 // k-blocks mod 4, added in class order, then the slices in slice order.
@@ -14,17 +14,18 @@
 // four LDS stages (global_load_lds, 1 KiB a wave: fragment order is what such
 // a load writes), so a stage costs no registers and one barrier.
 //
-// What bounds it: the operand tiles on their way into LDS.  The loads alone
-// take 296 of the 388 us of a 2048-row gate/up on 256x128 tiles, the MFMAs
-// alone 227 us (1.6 PFLOP/s, this card's matrix rate) and the LDS reads 120
-// us; each CU takes in 50-60 GB/s whatever the ring's depth (3 to 8 stages
-// measured) or the order of the tiles over the dies.  So the tile is as large
-// as the registers allow, 256x192 (28 KiB a k-block for 1.5 times the work of
-// 24 KiB): gate/up at 512 rows 107 -> 86 us, 1024 rows 187 -> 170 us, QKV at
-// 1024 rows 117 -> 94 us.  Against the streaming kernel, 7B shapes, us: 2048
-// rows QKV 477 -> 230, O 153 -> 68, gate/up 620 -> 365, down 319 -> 167; 256
-// rows QKV 46 -> 43, O 22 -> 16, gate/up 76 -> 61, down 43 -> 34, LM head 119
-// -> 75.  Fragments read a step ahead of their MFMAs were no faster.
+// What bounds it: the operand tiles on their way into LDS.  With 256x128 tiles
+// a 2048-row gate/up took 388 us; its loads alone took 296, its MFMAs alone 227
+// (1.6 PFLOP/s, this card's matrix rate), its LDS reads 120, and rings of 3 to
+// 8 stages or another order of the tiles over the dies changed nothing.  So the
+// tile is as large as the registers allow, 256x192 (28 KiB a k-block for 1.5
+// times the work of 24 KiB): that product 388 -> 365 us, gate/up at 512 rows
+// 107 -> 86, 1024 rows 187 -> 170, QKV at 1024 rows 117 -> 94.  Against the
+// streaming kernel, 7B shapes, us: 2048 rows QKV 477 -> 230, O 153 -> 68,
+// gate/up 620 -> 365, down 319 -> 167; 256 rows QKV 42 -> 40, O 28 -> 24 (with
+// the finishing pass), gate/up 75 -> 65, LM head 119 -> 76.  Fragments read a
+// step ahead of their MFMAs were no faster.  Where its tiles are too large for
+// the matrix the streaming kernel stays (gemm_wide_takes).
 #include <hip/hip_ext.h>
 
 #include <algorithm>
@@ -61,23 +62,23 @@ __device__ __forceinline__ void dma_tile(const char* src, char* lds) {
                                    (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
 
-// Waves WM x WN, each MT 16-row tiles x CB column blocks; NS ring stages.  SL:
+constexpr int NS = 4;  // ring stages
+
+// Waves WM x WN, each MT 16-row tiles x CB column blocks.  SL:
 // the workgroup runs all reduction slices and adds them (otherwise it runs the
 // one its place in the grid names).  AL: every class is a multiple of NS
 // k-blocks, so a class always starts at ring position 0.
-template <typename T, int KIND, int WM, int WN, int MT, int CB, int NS, bool SL, bool AL>
+template <typename T, int KIND, int WM, int WN, int MT, int CB, bool SL, bool AL>
 __global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_kernel(const GemmShape sh, const GemmEpi e,
                                                                                    int nrb, int ncb) {
   constexpr int VEC = ET<T>::VEC;
   constexpr int NW = WM * WN;
   constexpr int TA = WM * MT, TB = WN * CB, NT = TA + TB;  // 1 KiB tiles per stage
   constexpr int P = (NT + NW - 1) / NW;                    // of them per wave
-  static_assert(NS >= 3 && NS <= 8, "stages");
   // one array per stage, and every use of one names it at compile time: the
   // compiler then knows which loads a read of a stage has to wait for
   constexpr int SB = NT * 1024;
-  __shared__ __attribute__((aligned(1024))) char s0[SB], s1[SB], s2[SB], s3[NS > 3 ? SB : 16], s4[NS > 4 ? SB : 16],
-      s5[NS > 5 ? SB : 16], s6[NS > 6 ? SB : 16], s7[NS > 7 ? SB : 16];
+  __shared__ __attribute__((aligned(1024))) char s0[SB], s1[SB], s2[SB], s3[SB];
   __shared__ RowMeta rm[KIND == EPI_QKV ? 16 * TA : 1];
 
   if (sh.skip && *sh.skip == 0) return;
@@ -148,11 +149,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_ker
     if constexpr (k == 0) return s0;
     else if constexpr (k == 1) return s1;
     else if constexpr (k == 2) return s2;
-    else if constexpr (k == 3) return s3;
-    else if constexpr (k == 4) return s4;
-    else if constexpr (k == 5) return s5;
-    else if constexpr (k == 6) return s6;
-    else return s7;
+    else return s3;
   };
   // one stage: its own loads have landed (NS - 2 later stages still in
   // flight), every wave is past the stage before, whose buffer is refilled
@@ -178,11 +175,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_ker
     step_k(Int<PH>{});
     step_k(Int<PH + 1>{});
     step_k(Int<PH + 2>{});
-    if constexpr (NS > 3) step_k(Int<PH + 3>{});
-    if constexpr (NS > 4) step_k(Int<PH + 4>{});
-    if constexpr (NS > 5) step_k(Int<PH + 5>{});
-    if constexpr (NS > 6) step_k(Int<PH + 6>{});
-    if constexpr (NS > 7) step_k(Int<PH + 7>{});
+    step_k(Int<PH + 3>{});
   };
   auto run_class = [&](auto ph, int n) __attribute__((always_inline)) {
     constexpr int PH = decltype(ph)::value;
@@ -199,20 +192,12 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_ker
       r = n % NS;
       if (r > 0) step_k(Int<PH>{});
       if (r > 1) step_k(Int<PH + 1>{});
-      if (NS > 3 && r > 2) step_k(Int<PH + 2>{});
-      if (NS > 4 && r > 3) step_k(Int<PH + 3>{});
-      if (NS > 5 && r > 4) step_k(Int<PH + 4>{});
-      if (NS > 6 && r > 5) step_k(Int<PH + 5>{});
-      if (NS > 7 && r > 6) step_k(Int<PH + 6>{});
+      if (r > 2) step_k(Int<PH + 2>{});
     }
   };
   issue(s0, next_kb());
   issue(s1, next_kb());
-  if constexpr (NS > 3) issue(s2, next_kb());
-  if constexpr (NS > 4) issue(s3, next_kb());
-  if constexpr (NS > 5) issue(s4, next_kb());
-  if constexpr (NS > 6) issue(s5, next_kb());
-  if constexpr (NS > 7) issue(s6, next_kb());
+  issue(s2, next_kb());
   int phase = 0;
 #pragma unroll 1
   for (int sl = 0; sl < slices; ++sl) {
@@ -233,19 +218,7 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_ker
         if (phase == 0) run_class(Int<0>{}, n);
         else if (phase == 1) run_class(Int<1>{}, n);
         else if (phase == 2) run_class(Int<2>{}, n);
-        else if constexpr (NS > 3) {
-          if (phase == 3) run_class(Int<3>{}, n);
-          else if constexpr (NS > 4) {
-            if (phase == 4) run_class(Int<4>{}, n);
-            else if constexpr (NS > 5) {
-              if (phase == 5) run_class(Int<5>{}, n);
-              else if constexpr (NS > 6) {
-                if (phase == 6) run_class(Int<6>{}, n);
-                else if constexpr (NS > 7) run_class(Int<7>{}, n);
-              }
-            }
-          }
-        }
+        else run_class(Int<3>{}, n);
       }
       if constexpr (!AL) phase = (phase + n) % NS;
 #pragma unroll
@@ -301,10 +274,6 @@ __global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_ker
     }
   }
 }
-
-}  // namespace
-
-namespace {
 
 // Output tiles: rows x 16-column blocks per workgroup, and the time of one
 // round of a launch with them on 256 CUs (us, K = 4096).
@@ -380,7 +349,6 @@ double wide_us(int M, int nbc, int kps, int splits) {
 
 template <typename T, int KIND, int WM, int WN, int MT, int CB, bool SL>
 void go(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hipEvent_t eb) {
-  constexpr int NS = 4;
   const int nbc = s.nb_count ? s.nb_count : s.N / 16;
   const int nrb = (s.M + 16 * WM * MT - 1) / (16 * WM * MT), ncb = (nbc + WN * CB - 1) / (WN * CB);
   const int kps = s.K / (4 * ET<T>::VEC) / s.splits;
@@ -388,17 +356,17 @@ void go(const GemmShape& s, const GemmEpi& e, hipStream_t st, hipEvent_t ea, hip
   const bool al = kps % (4 * NS) == 0;
   if (ea || eb) {
     if (al)
-      hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, true>), grid, wg, 0, st, ea, eb, 0, s, e,
+      hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, SL, true>), grid, wg, 0, st, ea, eb, 0, s, e,
                             nrb, ncb);
     else if constexpr (CB < 6)
-      hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, false>), grid, wg, 0, st, ea, eb, 0, s,
+      hipExtLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, SL, false>), grid, wg, 0, st, ea, eb, 0, s,
                             e, nrb, ncb);
     return;
   }
   if (al)
-    hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, true>), grid, wg, 0, st, s, e, nrb, ncb);
+    hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, SL, true>), grid, wg, 0, st, s, e, nrb, ncb);
   else if constexpr (CB < 6)
-    hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, NS, SL, false>), grid, wg, 0, st, s, e, nrb, ncb);
+    hipLaunchKernelGGL((gemm_wide_kernel<T, KIND, WM, WN, MT, CB, SL, false>), grid, wg, 0, st, s, e, nrb, ncb);
 }
 
 template <int KIND>
