@@ -123,6 +123,15 @@ def step_marks(names):
     return out
 
 
+def prefill_span(names, before):
+    """First and last kernel of the prefill that ends before kernel `before`:
+    from the first prefill rows after the step before it to the last finish."""
+    end = max((i for i in range(before) if "prefill_finish_kernel" in names[i]), default=-1)
+    prev = max((i for i in range(end) if "stamp_kernel" in names[i]), default=-1)
+    rows = [i for i in range(prev + 1, end) if "prefill_rows_kernel" in names[i]]
+    return (rows[0], end) if rows else None
+
+
 # --------------------------------------------------------------------------
 def trace(d, wl_name, warmup, steps, cmd):
     import synth
@@ -222,6 +231,20 @@ def trace(d, wl_name, warmup, steps, cmd):
                "| us/step | launches/step | avg us | kernel |\n|---:|---:|---:|---|\n")
     for key, (us, c) in sorted(agg.items(), key=lambda kv: -kv[1][0]):
         out.append(f"| {us / ns:.1f} | {c / ns:.1f} | {us / c:.2f} | `{key}` |\n")
+    span = prefill_span([r["Kernel_Name"] for r in rows], spec[0][0])
+    if span:
+        agg = collections.defaultdict(lambda: [0.0, 0])
+        for r in rows[span[0]:span[1] + 1]:
+            agg[short(r["Kernel_Name"])][0] += (t(r, "End_Timestamp") - t(r, "Start_Timestamp")) / 1e3
+            agg[short(r["Kernel_Name"])][1] += 1
+        wall = (t(rows[span[1]], "End_Timestamp") - t(rows[span[0]], "Start_Timestamp")) / 1e3
+        tokens = sum(len(p) for p in wl.prompts())
+        out.append(f"\n## Kernels of the prefill before the steps\n\n{tokens} prompt tokens, first kernel to last "
+                   f"{wall:.0f} us, busy {sum(us for us, _ in agg.values()):.0f} us; kernels over 0.5%.\n\n"
+                   "| us | launches | avg us | kernel |\n|---:|---:|---:|---|\n")
+        for key, (us, c) in sorted(agg.items(), key=lambda kv: -kv[1][0]):
+            if us > 0.005 * wall:
+                out.append(f"| {us:.0f} | {c} | {us / c:.2f} | `{key}` |\n")
     stats = os.path.join(d, "run_kernel_stats.csv")
     if os.path.exists(stats):
         srows = sorted(csv.DictReader(open(stats)), key=lambda r: -float(r["TotalDurationNs"]))

@@ -6,6 +6,8 @@ its shape takes and by the tiled kernel with each of its output tiles, against
 the same rows in launches of at most 128 (the streaming kernel), and prompts
 prefilled together, in chunks of up to 2048 rows, against each prompt prefilled
 alone."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch  # before the library: both then share one HIP runtime
@@ -216,11 +218,16 @@ def _states(sess):
     ("small", (63, 129, 640)),
     ("small", (1500, 2, 900)),   # the third prompt is cut at a chunk's end
     ("small", (2049,)),          # one row past the largest chunk
+    # 7B width: 129, 506, 1017 and 2033 rows together, at most 128 (256 encoder
+    # rows) alone
+    ("7b", (128, 1)), ("7b", (128, 127, 126, 125)), ("7b", tuple(128 - i % 3 for i in range(8))),
+    ("7b", tuple(128 - i % 3 for i in range(16))),
 ])
 def test_prompts_prefilled_together_equal_each_alone(model, lens):
     print(f"packed prefill: {model}, prompts {lens}", flush=True)
-    cfg = synth.TINY if model == "tiny" else synth.small_config()
-    w = synth.make_weights(cfg, device="cuda", std=0.06)
+    cfg = {"tiny": synth.TINY, "small": synth.small_config(),
+           "7b": dataclasses.replace(synth.LLAMA7B, n_layers=1)}[model]
+    w = synth.make_weights(cfg, device="cuda", std=0.06 if cfg.d_model < 4096 else 0.02)
     prompts = [synth.make_prompt(n, cfg.vocab, 40 + i) for i, n in enumerate(lens)]
     max_len = max(lens) + 128
     every = Session(cfg, w, synth.TREE_T8, max_batch=len(lens), max_len=max_len)

@@ -97,6 +97,15 @@ def test_every_gemm_source_is_in_the_record():
     assert all(s in names for s in build.SOURCES if s.startswith("kernels_gemm"))
 
 
+def test_prefill_span_is_the_one_before_the_steps():
+    rows, gemm, fin, stamp = "prefill_rows_kernel<T>", "gemm_wide_kernel<T>", "prefill_finish_kernel", "stamp_kernel"
+    first = [rows, gemm, fin, "draft_rows_kernel<T>", stamp]          # another session's prefill and step
+    second = [rows, gemm, rows, gemm, fin, rows, gemm, fin]           # three chunks, prompts end in the last two
+    names = first + ["repack_kernel"] + second + ["draft_rows_kernel<T>", stamp]
+    assert ps.prefill_span(names, len(first) + 1 + len(second)) == (len(first) + 1, len(first) + len(second))
+    assert ps.prefill_span([stamp, gemm], 2) is None
+
+
 def test_gemm_counters_refuse_a_layer_count_mismatch(tmp_path, monkeypatch):
     monkeypatch.setattr(ps, "OUT_DIR", str(tmp_path))
     wl = synth.WORKLOADS["llama7b_p512"]
