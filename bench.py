@@ -189,8 +189,8 @@ def torch_gemm_reference(torch, dev, cfg, M, reps=40):
 
 def counter_traffic():
     """HBM bytes per verify-GEMM launch from the committed rocprofv3 counter
-    summary, if the GEMM's sources (the kernel file, the headers it
-    includes and the build script with its compiler flags) still have the
+    summary, if the GEMM's sources (the kernel files, the headers they
+    share and the build script with its compiler flags) still have the
     hash they were measured with."""
     import hashlib
     path = os.path.join(ROOT, "profiles", "verify_gemm_llama7b_p512_traffic.json")

@@ -1,9 +1,8 @@
-// Split-K GEMMs of a few rows in one launch (M <= 16, narrow matrices: the
-// draft's trigram encoder, down projection and head MLPs).  The streaming
-// kernel runs one workgroup per
-// reduction slice and leaves the slices to a finishing launch: with a few rows
-// a pass over some hundred KiB that costs as much as a fifth of the product
-// (3.8 us next to 15-20 us at 7B width).  Where the consumer adds the slices
+// Split-K GEMMs of a few rows in one launch (M <= 16: the draft's trigram
+// encoder, down projection and head MLPs).  The streaming kernel runs one
+// workgroup per reduction slice and leaves the slices to a finishing launch:
+// with a few rows a pass over some hundred KiB that costs as much as a fifth of
+// the product (3.8 us next to 15-20 us at 7B width).  Where the consumer adds the slices
 // anyway (the norms after O and down) it stays the faster one, 11.7 us against
 // 13.1 a launch in greedy decoding at 7B width.
 //

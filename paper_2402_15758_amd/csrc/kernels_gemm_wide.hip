@@ -1,18 +1,19 @@
 // GEMMs of more than 128 bf16 rows (prefill chunks, wide verify batches) over
-// matrices wide or deep enough: Y = X[M][K] @ W[K][N] on 2-D output tiles, with the operands of
-// kernels_gemm.hip (both in MFMA fragment order) and its summation order, bit
-// for bit: per reduction slice four partial sums, one per residue class of the
-// k-blocks mod 4, added in class order, then the slices in slice order.
+// matrices wide or deep enough: Y = X[M][K] @ W[K][N] on 2-D output tiles, with
+// the operands of kernels_gemm.hip (both in MFMA fragment order) and its
+// summation order, bit for bit: per reduction slice four partial sums, one per
+// residue class of the k-blocks mod 4, added in class order, then the slices in
+// slice order.
 //
 // The streaming kernel gives each of its four waves one class, so a workgroup
-// re-reads its activation rows for every run of 6 columns blocks: fine while
+// re-reads its activation rows for every run of 6 column blocks: fine while
 // the weight stream is what is waited for, and 430-600 TFLOP/s on 2048 rows.
 // Here a workgroup owns a tile of up to 256 rows x 192 columns, its eight
 // waves 64 x 64 (two a SIMD: 64 accumulators, 64 totals and, with the slices
-// added in registers, 64 sums fit their 256 registers) or 64 x 96, and the classes run
-// one after another.  Operand tiles go from memory straight into a ring of
-// four LDS stages (global_load_lds, 1 KiB a wave: fragment order is what such
-// a load writes), so a stage costs no registers and one barrier.
+// added in registers, 64 sums fit their 256 registers) or 64 x 96, and the
+// classes run one after another.  Operand tiles go from memory straight into a
+// ring of four LDS stages (global_load_lds, 1 KiB a wave: fragment order is what
+// such a load writes), so a stage costs no registers and one barrier.
 //
 // What bounds it: the operand tiles on their way into LDS.  With 256x128 tiles
 // a 2048-row gate/up took 388 us; its loads alone took 296, its MFMAs alone 227
@@ -64,10 +65,10 @@ __device__ __forceinline__ void dma_tile(const char* src, char* lds) {
 
 constexpr int NS = 4;  // ring stages
 
-// Waves WM x WN, each MT 16-row tiles x CB column blocks.  SL:
-// the workgroup runs all reduction slices and adds them (otherwise it runs the
-// one its place in the grid names).  AL: every class is a multiple of NS
-// k-blocks, so a class always starts at ring position 0.
+// Waves WM x WN, each MT 16-row tiles x CB column blocks.  SL: the workgroup
+// runs all reduction slices and adds them (otherwise it runs the one its place
+// in the grid names).  AL: every class is a multiple of NS k-blocks, so a class
+// always starts at ring position 0.
 template <typename T, int KIND, int WM, int WN, int MT, int CB, bool SL, bool AL>
 __global__ __launch_bounds__(64 * WM * WN, (WM * WN + 3) / 4) void gemm_wide_kernel(const GemmShape sh, const GemmEpi e,
                                                                                    int nrb, int ncb) {
